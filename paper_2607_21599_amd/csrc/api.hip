@@ -11,6 +11,7 @@
 
 #include "daf.h"
 #include "daf_internal.h"
+#include "gemm.h"
 
 namespace {
 
@@ -588,24 +589,28 @@ LayerWs layer_ws(const Cfg &c, const daf_layer_weights_t &w, const Batch &b, int
   l.m = take(r * w.inter * e);
   l.attn_bytes = mode == DAF_LAYER_DAF ? ws_layout(c, b, plan_splits(c, b)).total : 0;
   l.attn = take(l.attn_bytes);
-  l.part = take(kGemmPartBytes);  // fp32 k pieces of the projections' tail tiles
+  l.part = take(kGemmPieceBytes);  // fp32 k pieces of the projections' last tiles
   l.total = off;
   return l;
 }
 
-// part: workspace for the k pieces of tail tiles (kGemmPartBytes), or null
-daf_status_t gemm(int64_t M, int N, int K, const void *A, const void *W, const void *bias, const void *res, void *C,
-                  hipStream_t st, float *part = nullptr) {
-  GemmArgs g{};
+// C = A W^T (+ bias) (+ residual), or gated (one segment of N gated columns).
+GemmJob gemm_job(int64_t M, int N, int K, const void *A, const void *W, const void *bias, const void *res, void *C,
+                 bool glu = false) {
+  GemmJob g{};
   g.A = A;
-  g.W = W;
-  g.bias = bias;
   g.residual = res;
-  g.C = C;
   g.M = M;
-  g.N = N;
   g.K = K;
-  const hipError_t e = part ? launch_gemm_split(g, part, kGemmPartBytes, st) : launch_gemm(g, st);
+  g.n_segs = 1;
+  g.glu = glu;
+  g.seg[0] = GemmSeg{W, bias, C, N};
+  return g;
+}
+
+// part: workspace for fp32 pieces of tiles cut along k (kGemmPieceBytes), or null
+daf_status_t run_gemm(const GemmJob &g, hipStream_t st, float *part = nullptr) {
+  const hipError_t e = launch_gemm_job(g, part, part ? kGemmPieceBytes : 0, st);
   return e == hipSuccess ? DAF_OK : hip_fail(e, "linear launch");
 }
 
@@ -786,17 +791,7 @@ daf_status_t daf_linear(int64_t M, int32_t N, int32_t K, const void *A, const vo
     CHECK(need_ptr(C, "C"));
     if (bias) CHECK(need_ptr(bias, "bias"));
     if (residual) CHECK(need_ptr(residual, "residual"));
-    GemmArgs g{};
-    g.A = A;
-    g.W = W;
-    g.bias = bias;
-    g.residual = residual;
-    g.C = C;
-    g.M = M;
-    g.N = N;
-    g.K = K;
-    const hipError_t e = launch_gemm(g, stream);
-    if (e != hipSuccess) return hip_fail(e, "linear launch");
+    CHECK(run_gemm(gemm_job(M, N, K, A, W, bias, residual, C), stream));
     return ok();
   } catch (...) {
     return fail(DAF_ERR_HIP, "unexpected host exception");
@@ -814,16 +809,8 @@ daf_status_t daf_linear_swiglu(int64_t M, int32_t I, int32_t K, const void *A, c
     CHECK(need_ptr(A, "A"));
     CHECK(need_ptr(Wgu, "Wgu"));
     CHECK(need_ptr(C, "C"));
-    GemmArgs g{};
-    g.A = A;
-    g.W = Wgu;
-    g.C = C;
-    g.M = M;
-    g.N = I;
-    g.K = K;
-    g.glu = 1;
-    const hipError_t e = launch_gemm(g, stream);
-    return e == hipSuccess ? ok() : hip_fail(e, "linear launch");
+    CHECK(run_gemm(gemm_job(M, I, K, A, Wgu, nullptr, nullptr, C, true), stream));
+    return ok();
   } catch (...) {
     return fail(DAF_ERR_HIP, "unexpected host exception");
   }
@@ -926,9 +913,12 @@ daf_status_t daf_decoder_layer(const daf_attn_cfg_t *cfg, const daf_layer_weight
     const hipError_t e0 = launch_rmsnorm(R, H, x, w->w_in, w->eps, h, stream);
     if (e0 != hipSuccess) return hip_fail(e0, "rmsnorm launch");
     float *part = reinterpret_cast<float *>(ws + l.part);
-    CHECK(gemm(R, QW, H, h, w->wq, w->bq, nullptr, q, stream, part));
-    CHECK(gemm(R, KW, H, h, w->wk, w->bk, nullptr, k, stream, part));
-    CHECK(gemm(R, KW, H, h, w->wv, w->bv, nullptr, v, stream, part));
+    {  // the Q, K and V projections in one launch
+      GemmJob g = gemm_job(R, QW, H, h, w->wq, w->bq, nullptr, q);
+      g.seg[g.n_segs++] = GemmSeg{w->wk, w->bk, k, KW};
+      g.seg[g.n_segs++] = GemmSeg{w->wv, w->bv, v, KW};
+      CHECK(run_gemm(g, stream, part));
+    }
     hipError_t e1 = launch_rope(R, c.hq, c.d, QW, q, pos, w->rope_theta, stream);
     if (e1 == hipSuccess) e1 = launch_rope(R, c.hkv, c.d, KW, k, pos, w->rope_theta, stream);
     if (e1 != hipSuccess) return hip_fail(e1, "rope launch");
@@ -967,22 +957,12 @@ daf_status_t daf_decoder_layer(const daf_attn_cfg_t *cfg, const daf_layer_weight
       }
       CHECK(run_entries(c, AttnKind::kSelf, entries, stream));
     }
-    CHECK(gemm(R, H, QW, o, w->wo, nullptr, x, x, stream, part));
+    CHECK(run_gemm(gemm_job(R, H, QW, o, w->wo, nullptr, x, x), stream, part));
     const hipError_t e2 = launch_rmsnorm(R, H, x, w->w_post, w->eps, h, stream);
     if (e2 != hipSuccess) return hip_fail(e2, "rmsnorm launch");
-    {  // gate and up projections with SiLU(gate) * up in the epilogue
-      GemmArgs g{};
-      g.A = h;
-      g.W = w->wgu;
-      g.C = m;
-      g.M = R;
-      g.N = I;
-      g.K = H;
-      g.glu = 1;
-      const hipError_t e3 = launch_gemm(g, stream);
-      if (e3 != hipSuccess) return hip_fail(e3, "linear launch");
-    }
-    CHECK(gemm(R, H, I, m, w->wd, nullptr, x, x, stream, part));
+    // gate and up projections with SiLU(gate) * up in the epilogue
+    CHECK(run_gemm(gemm_job(R, I, H, h, w->wgu, nullptr, nullptr, m, true), stream));
+    CHECK(run_gemm(gemm_job(R, H, I, m, w->wd, nullptr, x, x), stream, part));
     return ok();
   } catch (...) {
     return fail(DAF_ERR_HIP, "unexpected host exception");

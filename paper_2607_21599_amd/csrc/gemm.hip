@@ -5,408 +5,538 @@
 // the QKV computation phase; Sec. 2 item 3: the fused compact state feeds the
 // next layer's projections).
 //
-// Both operands are K-contiguous, which is how the matrix cores take them: a
-// 32x32x16 bf16 MFMA reads, per lane, 8 consecutive k of one row of each
-// operand. Workgroup tile 128 (M) x 128 (N), k steps of 64; 4 waves of 64 x 64
-// (2 x 2 MFMA blocks). The A and W tiles of a k step are copied global -> LDS
-// with the buffer unit (rows of 128 B, 16-byte chunks XOR-swizzled by
-// (row >> 1) & 7 so that the 16 lanes of a read phase hit distinct banks),
-// double-buffered so the copy of step k+1 overlaps the MFMAs of step k. The
-// accumulators are staged through LDS in fp32 so that bias, residual and the
-// bf16 stores run on whole 128-byte row segments.
+// Tile: 256 (M) x 256 (N), k steps of 64, one workgroup of 8 waves per CU. The
+// waves form two groups of four (rows 64 wm .. of each 128-row half, wm = wave
+// / 4; two waves of different groups share a SIMD) that run half a phase
+// apart: while one group issues the MFMAs of a phase, the other reads its LDS
+// fragments and issues its global -> LDS copies, with a barrier between, so
+// the matrix cores always have one wave's MFMAs and the other wave's loads are
+// off their critical path. A k step has four phases, one per quadrant of the
+// wave's 128 x 64 block:
+//   (rows half 0, columns 0-31), (0, 32-63), (1, 32-63), (1, 0-31)
+// so that only one operand fragment set changes per phase.
 //
-// Tile order: the tiles are split into 8 contiguous ranges, one per XCD
-// (workgroup i runs on XCD i mod 8); within a range, groups of 8 M-tiles sweep
-// the N-tiles, so the A rows of a group stay in that XCD's L2 while W streams.
+// Both operands are K-contiguous, as the matrix cores take them. LDS holds two
+// k steps as 16 KiB regions of 128 rows x 128 bytes (A rows half 0 / half 1, W
+// columns 0-31 / 32-63 of every wave), 16-byte chunks XOR-swizzled by
+// (row / 2) mod 8: no bank conflicts (SQ_LDS_BANK_CONFLICT = 0). A region is
+// copied again two phases after its fragments were read (by then both groups
+// have read it) and is waited for six phases after its copy was issued with a
+// counted s_waitcnt vmcnt: the five younger copies stay in flight across the
+// barriers. The previous kernel waited for every copy once per k step.
+//
+// What bounds it: the chip's power. At 8192^3 the matrix cores are busy 83% of
+// the cycles, but at a shader clock of 1.5-1.6 GHz; the instruction that needs
+// less power per FLOP runs faster. v_mfma_f32_16x16x32_bf16 reads and writes
+// half the accumulator registers per FLOP of v_mfma_f32_32x32x16_bf16: the
+// same kernel ran 868 us with 32x32x16 and 732 us with 16x16x32 (1502
+// TFLOP/s; the previous 2-stage kernel with 32x32x16 ~1150). 64-byte rows per
+// copy (k steps of 32, four stages) doubled the L2 requests: 911 us.
+//
+// Work list (plan_job): whole rounds of 256 tiles, one per CU, then the rest:
+// row ranges of at most 128 rows and, where that shortens the last round,
+// tiles of the last round cut in two 128 x 256 tiles (two phases per k step,
+// three LDS stages) and, given a workspace, cut along k, all in the same
+// launch after the whole tiles.
 #include <algorithm>
 
 #include "daf_internal.h"
+#include "gemm.h"
 
 namespace daf {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 
-constexpr int kTK = 64;                         // k step
-constexpr int kRowB = kTK * 2;                  // bytes per tile row in LDS
-constexpr int kGroupM = 8;                      // M-tiles per group of the tile order
+constexpr int kTK = 64;          // k step
+constexpr int kRegion = 16384;   // LDS region: 128 rows x 128 bytes
+constexpr int kGroupM = 8;       // M-tiles per group of the tile order
+constexpr int kCus = 256;
 [[maybe_unused]] constexpr int kRsrcWord3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 
-__device__ __forceinline__ int swz(int r) { return (r >> 1) & 7; }
-
-// Tile shape: workgroup TM x TN, waves of WM x WN (TM/WM x TN/WN waves).
-template <int TM_, int TN_, int WM_, int WN_>
-struct Shape {
-  static constexpr int TM = TM_, TN = TN_, WM = WM_, WN = WN_;
-  static constexpr int WAVES_M = TM / WM, WAVES = WAVES_M * (TN / WN), THREADS = 64 * WAVES;
-  static constexpr int MB = WM / 32, NB = WN / 32;           // 32x32 MFMA blocks per wave
-  static constexpr int A_IPW = TM / WAVES / 8, B_IPW = TN / WAVES / 8;  // copy instructions per wave
-  static constexpr int ATILE = TM * kRowB, BTILE = TN * kRowB;
-  // fp32 staging of the epilogue: rows per pass so that a wave's share fits
-  // its part of the LDS (2 (ATILE + BTILE) / WAVES bytes, 256 B per row)
-  static constexpr int STAGE_B = 2 * (ATILE + BTILE) / WAVES;
-  static constexpr int PASS_ROWS = (STAGE_B / (WN * 4)) < WM ? (STAGE_B / (WN * 4)) : WM;
-  static_assert(WN == 64, "the epilogue stages 64-column rows");
-  static_assert(TM % (WAVES * 8) == 0 && TN % (WAVES * 8) == 0, "copy split");
-  static_assert(WM % PASS_ROWS == 0 && PASS_ROWS % 8 == 0, "staging passes");
+struct GemmPlan {
+  GemmJob j;
+  int32_t tn;          // column tiles over all segments
+  int32_t seg_tn[kMaxGemmSegs];
+  int32_t tiles_m;     // 256-row tiles (the last may hold 129-255 rows)
+  int32_t n_full;      // 256-row tiles run whole, in tile order
+  int32_t n_cut;       // the tiles after them, run as two halves each
+  int32_t n_half;      // 128-row units: 2 n_cut, then one per column tile if <= 128 rows remain
+  int32_t k_parts;     // pieces per 128-row unit along k
+  float *part;         // k_parts > 1: [unit][piece][128][256] fp32
 };
 
-// Copy ROWS rows x 64 columns (rows at `base`, pitch `row_bytes`) into LDS;
-// this wave copies IPW x 8 rows starting at row first_row. Rows at or past
-// `nrec` bytes read as zero.
-template <int IPW>
-__device__ __forceinline__ void copy_tile(const unsigned char *base, int nrec, unsigned char *lds, int first_row,
-                                          const int (&voff)[IPW]) {
+template <int N>
+__device__ __forceinline__ void wait_vm() {
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x0F70);  // vmcnt(N); the other counters at their maxima
+}
+// A workgroup barrier that neither memory operations nor MFMAs move across;
+// unlike __syncthreads it waits for no memory operation.
+__device__ __forceinline__ void phase_barrier() {
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("s_barrier" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Copy a region: this wave writes rows 16 wave .. 16 wave + 15 (two 1 KiB
+// instructions); bytes at or past `nrec` from `base` read as zero.
+__device__ __forceinline__ void copy_region(const unsigned char *base, uint32_t nrec, unsigned char *lds, int wave,
+                                            const uint32_t (&voff)[2]) {
 #if defined(__HIP_DEVICE_COMPILE__)
   const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, nrec, kRsrcWord3);
 #pragma unroll
-  for (int i = 0; i < IPW; ++i)
+  for (int i = 0; i < 2; ++i)
     __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        r, (void __attribute__((address_space(3))) *)((lds_u8 *)lds + (first_row + i * 8) * kRowB), 16, voff[i], 0,
-        0, 0);
+        r, (void __attribute__((address_space(3))) *)((lds_u8 *)lds + (wave * 2 + i) * 1024), 16, (int)voff[i], 0, 0,
+        0);
 #endif
 }
 
-// One k step: the MB x NB x 4 MFMAs of this wave on the tiles in (as, bs).
-// The fragment reads of each half of the step (two k16 slices) go out before
-// its MFMAs, so the MFMAs of one slice run while the next reads land.
-template <class S>
-__device__ __forceinline__ void mma_step(f32x16 (&acc)[S::MB][S::NB], const unsigned char *as,
-                                         const unsigned char *bs, const int (&fa)[S::MB][4],
-                                         const int (&fb)[S::NB][4]) {
+// Per-wave state of a tile of H 128-row halves.
+template <int H>
+struct Tile {
+  f32x4 acc[H][2][4][2];  // [row half][column half][16 rows][16 columns], D^T blocks: a lane holds 4 columns of a row
+  bf16x8 a[4][2];         // fragments of one row half: [16 rows][32 k]
+  bf16x8 b0[2][2][2], b1[2][2];  // column halves 0 (two sets) and 1: [16 columns][32 k]
+  int fa[2], fb[2];       // LDS read offsets per 32 k
+  uint32_t va[2], vb[2];  // copy source offsets
+  const unsigned char *A, *W0, *W1;  // tile origin; the two column halves' weight rows
+  uint32_t na, nb0, nb1;  // valid bytes from A, W0, W1
+  uint32_t a_half;        // bytes from row half 0 to 1
+  int wave, kt1;          // k steps of this piece
+
+  __device__ __forceinline__ void read_a(const unsigned char *r) {
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    bf16x8 a[2][S::MB], b[2][S::NB];
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-    for (int kk = 0; kk < 2; ++kk) {
+      for (int m = 0; m < 4; ++m) a[m][ks] = *reinterpret_cast<const bf16x8 *>(r + fa[ks] + m * 16 * 128);
+  }
+  __device__ __forceinline__ void read_b(bf16x8 (&b)[2][2], const unsigned char *r) {
 #pragma unroll
-      for (int j = 0; j < S::MB; ++j) a[kk][j] = *reinterpret_cast<const bf16x8 *>(as + fa[j][2 * h + kk]);
+    for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int j = 0; j < S::NB; ++j) b[kk][j] = *reinterpret_cast<const bf16x8 *>(bs + fb[j][2 * h + kk]);
+      for (int n = 0; n < 2; ++n) b[n][ks] = *reinterpret_cast<const bf16x8 *>(r + fb[ks] + n * 16 * 128);
+  }
+  __device__ __forceinline__ void mma(f32x4 (&c)[4][2], const bf16x8 (&b)[2][2]) {
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int m = 0; m < 4; ++m)
+#pragma unroll
+        for (int n = 0; n < 2; ++n) c[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[n][ks], a[m][ks], c[m][n], 0, 0, 0);
+  }
+  // Copies of k step kt; steps past the last read nothing and write zeros (no
+  // fragment of them is used), which keeps the count of copies in flight.
+  __device__ __forceinline__ void copy_a(int h, int kt, unsigned char *r) {
+    const uint32_t off = h * a_half + (uint32_t)kt * 128;
+    copy_region(A + off, kt < kt1 && na > off ? na - off : 0, r, wave, va);
+  }
+  __device__ __forceinline__ void copy_b(int h, int kt, unsigned char *r) {
+    const uint32_t off = (uint32_t)kt * 128, n = h ? nb1 : nb0;
+    copy_region((h ? W1 : W0) + off, kt < kt1 && n > off ? n - off : 0, r, wave, vb);
+  }
+};
+
+// Between a phase's reads and its MFMAs: the region the next phase reads has
+// landed (all but the N youngest copies of this wave), then every wave's has;
+// the fragments read in this phase are in registers.
+template <int N>
+__device__ __forceinline__ void enter_mma() {
+  wait_vm<N>();
+  phase_barrier();
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// One k step of a 256-row tile, T its parity. A0, A1, B1, B0: this step's
+// regions (B0 was read in the previous step's last phase); A1n, B0n: the next
+// step's.
+template <int T>
+__device__ __forceinline__ void step_full(Tile<2> &s, int kt, unsigned char *A0, unsigned char *A1, unsigned char *B0,
+                                          unsigned char *B1, unsigned char *A1n, unsigned char *B0n) {
+  s.read_a(A0);
+  s.copy_a(1, kt + 1, A1n);
+  enter_mma<10>();
+  s.mma(s.acc[0][0], s.b0[T]);
+  phase_barrier();
+  s.read_b(s.b1, B1);
+  s.copy_b(0, kt + 2, B0);
+  enter_mma<10>();
+  s.mma(s.acc[0][1], s.b1);
+  phase_barrier();
+  s.read_a(A1);
+  s.copy_a(0, kt + 2, A0);
+  enter_mma<10>();
+  s.mma(s.acc[1][1], s.b1);
+  phase_barrier();
+  s.read_b(s.b0[T ^ 1], B0n);
+  s.copy_b(1, kt + 2, B1);
+  enter_mma<10>();
+  s.mma(s.acc[1][0], s.b0[T]);
+  phase_barrier();
+}
+
+// One k step of a 128-row tile: A, B1, B0 this step's regions, Ap and B1p the
+// previous step's (= step kt + 2), B0n the next step's.
+__device__ __forceinline__ void step_half(Tile<1> &s, int kt, unsigned char *A, unsigned char *B0, unsigned char *B1,
+                                          unsigned char *Ap, unsigned char *B1p, unsigned char *B0n) {
+  s.read_a(A);
+  s.copy_a(0, kt + 2, Ap);
+  enter_mma<8>();
+  s.mma(s.acc[0][0], s.b0[0]);
+  phase_barrier();
+  s.read_b(s.b1, B1);
+  s.read_b(s.b0[0], B0n);
+  s.copy_b(1, kt + 2, B1p);
+  s.copy_b(0, kt + 3, B0);
+  enter_mma<10>();
+  s.mma(s.acc[0][1], s.b1);
+  phase_barrier();
+}
+
+struct Lds {
+  unsigned char *r[9];
+};
+
+// One tile: rows m0 .. of H 128-row halves, column tile tc, k piece kp.
+template <int H, bool GLU>
+__device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, int unit, int kp, int k_parts,
+                                         const Lds L) {
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int l16 = lane & 15, quad = lane >> 4, wm = wave >> 2, wn = wave & 3;
+  int si = 0;
+  while (si + 1 < p.j.n_segs && tc >= p.seg_tn[si]) tc -= p.seg_tn[si++];
+  const GemmSeg &S = p.j.seg[si];
+  constexpr int TN = GLU ? 128 : 256;  // output columns per tile
+  const int n0 = tc * TN, N = S.N;
+  const uint32_t rb = (uint32_t)p.j.K * 2;
+  const int KT = p.j.K / kTK, k0 = (int)((int64_t)kp * KT / k_parts), k1 = (int)((int64_t)(kp + 1) * KT / k_parts);
+  Tile<H> s;
+  s.wave = wave;
+  s.kt1 = k1 - k0;
+  const uint32_t ko = (uint32_t)k0 * 128;
+  const uint32_t rows = (uint32_t)min((int64_t)128 * H, p.j.M - m0);
+  s.A = static_cast<const unsigned char *>(p.j.A) + m0 * rb + ko;
+  s.na = rows * rb - ko;
+  s.a_half = 128 * rb;
+  const unsigned char *W = static_cast<const unsigned char *>(S.W) + ko;
+  const uint32_t cols = (uint32_t)min(TN, N - n0);
+  if (GLU) {  // column half 0: gate rows, half 1: the matching up rows
+    s.W0 = W + (int64_t)n0 * rb;
+    s.W1 = W + ((int64_t)N + n0) * rb;
+    s.nb0 = s.nb1 = cols * rb - ko;
+  } else {    // column half h of wave wn: columns 64 wn + 32 h ..
+    s.W0 = W + (int64_t)n0 * rb;
+    s.W1 = s.W0 + 32 * (int64_t)rb;
+    s.nb0 = cols * rb - ko;
+    s.nb1 = s.nb0 - 32 * rb;
+  }
+#pragma unroll
+  for (int i = 0; i < 2; ++i) {
+    const uint32_t r = wave * 16 + i * 8 + lane / 8;
+    const uint32_t c = ((lane & 7) ^ ((r >> 1) & 7)) << 4;
+    s.va[i] = r * rb + c;
+    s.vb[i] = (GLU ? r : (r >> 5) * 64 + (r & 31)) * rb + c;
+  }
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const int c = ((4 * ks + quad) ^ ((l16 >> 1) & 7)) << 4;
+    s.fa[ks] = (wm * 64 + l16) * 128 + c;
+    s.fb[ks] = (wn * 32 + l16) * 128 + c;
+  }
+#pragma unroll
+  for (int h = 0; h < H; ++h)
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
+#pragma unroll
+      for (int m = 0; m < 4; ++m) s.acc[h][j][m][0] = s.acc[h][j][m][1] = f32x4{};
+
+  // The copies run in the order in which the phases read the regions. Group 1
+  // then falls half a phase behind; group 0 waits for it at the end.
+  int kt = 0;
+  if constexpr (H == 2) {
+    // regions 0-3: A0 A1 B0 B1 of even k steps, 4-7 of odd ones
+    s.copy_b(0, 0, L.r[2]);
+    s.copy_a(0, 0, L.r[0]);
+    s.copy_b(1, 0, L.r[3]);
+    s.copy_a(1, 0, L.r[1]);
+    s.copy_b(0, 1, L.r[6]);
+    s.copy_a(0, 1, L.r[4]);
+    s.copy_b(1, 1, L.r[7]);
+    wait_vm<10>();
+    phase_barrier();
+    s.read_b(s.b0[0], L.r[2]);
+    if (wm) phase_barrier();
+    for (;;) {
+      step_full<0>(s, kt, L.r[0], L.r[1], L.r[2], L.r[3], L.r[5], L.r[6]);
+      if (++kt == s.kt1) break;
+      step_full<1>(s, kt, L.r[4], L.r[5], L.r[6], L.r[7], L.r[1], L.r[2]);
+      if (++kt == s.kt1) break;
     }
-#pragma unroll
-    for (int kk = 0; kk < 2; ++kk)
-      // D^T blocks: rows are output columns (W rows), columns output rows (A rows)
-#pragma unroll
-      for (int mb = 0; mb < S::MB; ++mb)
-#pragma unroll
-        for (int nb = 0; nb < S::NB; ++nb)
-          acc[mb][nb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(b[kk][nb], a[kk][mb], acc[mb][nb], 0, 0, 0);
-    __builtin_amdgcn_sched_group_barrier(0x100, 2 * (S::MB + S::NB), 0);  // this half's LDS reads
-    __builtin_amdgcn_sched_group_barrier(0x008, 2 * S::MB * S::NB, 0);    // then its MFMAs
-  }
-}
-
-template <class S>
-__device__ __forceinline__ void k_step(f32x16 (&acc)[S::MB][S::NB], int b_rows_bytes, const unsigned char *as,
-                                       const unsigned char *bs, unsigned char *an, unsigned char *bn,
-                                       const unsigned char *Ab, const unsigned char *Wb, int a_rows_bytes, int kt,
-                                       bool prefetch, int wave, const int (&va)[S::A_IPW],
-                                       const int (&vb)[S::B_IPW], const int (&fa)[S::MB][4],
-                                       const int (&fb)[S::NB][4]) {
-  // this wave's copies of step kt have landed; after the barrier every
-  // wave's have, and every wave is done reading the other buffers (step kt-1)
-  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0); expcnt and lgkmcnt left at their maxima
-  __syncthreads();
-  if (prefetch) {
-    const int kb = (kt + 1) * kRowB;
-    copy_tile<S::A_IPW>(Ab + kb, a_rows_bytes - kb, an, wave * S::A_IPW * 8, va);
-    copy_tile<S::B_IPW>(Wb + kb, b_rows_bytes - kb, bn, wave * S::B_IPW * 8, vb);
-  }
-  mma_step<S>(acc, as, bs, fa, fb);
-}
-
-// Output tile t of the tile order: groups of kGroupM M-tiles sweep the N-tiles.
-__device__ __forceinline__ void tile_coords(const GemmArgs &p, int t, int &tm, int &tn) {
-  const int span = kGroupM * p.tiles_n;
-  const int first_m = (t / span) * kGroupM;
-  const int gsize = min(p.tiles_m - first_m, kGroupM);
-  tm = first_m + (t % span) % gsize;
-  tn = (t % span) / gsize;
-}
-
-// GLU: the tile's TN W rows are TN/2 gate rows and the matching TN/2 up rows
-// (N rows further), so the workgroup produces TN/2 gated output columns.
-// PARTIAL: one k piece of a tail tile, its fp32 sums stored to p.part.
-template <class S, bool GLU, bool PARTIAL = false>
-__global__ __launch_bounds__(S::THREADS, 2) void gemm_bf16_kernel(const GemmArgs p) {
-  __shared__ __attribute__((aligned(1024))) unsigned char a_lds0[S::ATILE];
-  __shared__ __attribute__((aligned(1024))) unsigned char b_lds0[S::BTILE];
-  __shared__ __attribute__((aligned(1024))) unsigned char a_lds1[S::ATILE];
-  __shared__ __attribute__((aligned(1024))) unsigned char b_lds1[S::BTILE];
-
-  // ---- which tile ---------------------------------------------------------------
-  // whole tiles: the launch's range of the tile order is cut into 8 contiguous
-  // ranges, one per XCD (workgroup i runs on XCD i mod 8); k pieces of tail
-  // tiles: workgroup i runs piece i mod k_parts of tile t_begin + i / k_parts
-  int t, kp = 0;
-  if (PARTIAL) {
-    if ((int)blockIdx.x >= p.t_count * p.k_parts) return;
-    t = p.t_begin + blockIdx.x / p.k_parts;
-    kp = blockIdx.x % p.k_parts;
   } else {
-    const int count = p.t_count > 0 ? p.t_count : p.tiles_m * p.tiles_n;
-    const int per_xcd = (count + kXcds - 1) / kXcds;
-    const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
-    if (xcd * per_xcd + slot >= count) return;
-    t = p.t_begin + xcd * per_xcd + slot;
-  }
-  int tm, tn;
-  tile_coords(p, t, tm, tn);
-
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63, l32 = lane & 31, half = lane >> 5;
-  const int wm = wave % S::WAVES_M, wn = wave / S::WAVES_M;
-  const int64_t m0 = (int64_t)tm * S::TM;
-  constexpr int OUT_TN = GLU ? S::TN / 2 : S::TN;  // output columns per tile
-  const int n0 = tn * OUT_TN;
-  const int row_bytes = p.K * 2;
-  const int rows_valid = (int)min((int64_t)S::TM, p.M - m0);
-  const unsigned char *Ab = static_cast<const unsigned char *>(p.A) + m0 * row_bytes;
-  const unsigned char *Wb = static_cast<const unsigned char *>(p.W) + (int64_t)n0 * row_bytes;
-  const int a_rows_bytes = rows_valid * row_bytes;  // A rows past M read as zero
-  // W rows the tile reaches from Wb: TN, or up to the last up row in GLU mode
-  const int b_rows_bytes = (GLU ? p.N + S::TN / 2 : S::TN) * row_bytes;
-
-  int va[S::A_IPW], vb[S::B_IPW];
-#pragma unroll
-  for (int i = 0; i < S::A_IPW; ++i) {
-    const int r = (wave * S::A_IPW + i) * 8 + lane / 8;
-    va[i] = r * row_bytes + (((lane & 7) ^ swz(r)) << 4);
-  }
-#pragma unroll
-  for (int i = 0; i < S::B_IPW; ++i) {
-    const int r = (wave * S::B_IPW + i) * 8 + lane / 8;
-    const int g = GLU && r >= S::TN / 2 ? p.N + r - S::TN / 2 : r;  // W row relative to Wb
-    vb[i] = g * row_bytes + (((lane & 7) ^ swz(r)) << 4);
-  }
-  int fa[S::MB][4], fb[S::NB][4];
-#pragma unroll
-  for (int ks = 0; ks < 4; ++ks) {
-#pragma unroll
-    for (int j = 0; j < S::MB; ++j) {
-      const int ra = wm * S::WM + j * 32 + l32;
-      fa[j][ks] = ra * kRowB + (((2 * ks + half) ^ swz(ra)) << 4);
-    }
-#pragma unroll
-    for (int j = 0; j < S::NB; ++j) {
-      const int rb = wn * S::WN + j * 32 + l32;
-      fb[j][ks] = rb * kRowB + (((2 * ks + half) ^ swz(rb)) << 4);
+    // stage j = k step mod 3: A = region 3j, B0 = 3j + 1, B1 = 3j + 2
+    s.copy_b(0, 0, L.r[1]);
+    s.copy_a(0, 0, L.r[0]);
+    s.copy_b(1, 0, L.r[2]);
+    s.copy_b(0, 1, L.r[4]);
+    s.copy_a(0, 1, L.r[3]);
+    s.copy_b(1, 1, L.r[5]);
+    s.copy_b(0, 2, L.r[7]);
+    wait_vm<10>();
+    phase_barrier();
+    s.read_b(s.b0[0], L.r[1]);
+    if (wm) phase_barrier();
+    for (;;) {
+      step_half(s, kt, L.r[0], L.r[1], L.r[2], L.r[6], L.r[8], L.r[4]);
+      if (++kt == s.kt1) break;
+      step_half(s, kt, L.r[3], L.r[4], L.r[5], L.r[0], L.r[2], L.r[7]);
+      if (++kt == s.kt1) break;
+      step_half(s, kt, L.r[6], L.r[7], L.r[8], L.r[3], L.r[5], L.r[1]);
+      if (++kt == s.kt1) break;
     }
   }
-
-  f32x16 acc[S::MB][S::NB];
-#pragma unroll
-  for (int mb = 0; mb < S::MB; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < S::NB; ++nb) acc[mb][nb] = f32x16{};
-
-  const int KT = p.K / kTK;
-  const int kt0 = PARTIAL ? kp * KT / p.k_parts : 0, kt1 = PARTIAL ? (kp + 1) * KT / p.k_parts : KT;
-  copy_tile<S::A_IPW>(Ab + kt0 * kRowB, a_rows_bytes - kt0 * kRowB, a_lds0, wave * S::A_IPW * 8, va);
-  copy_tile<S::B_IPW>(Wb + kt0 * kRowB, b_rows_bytes - kt0 * kRowB, b_lds0, wave * S::B_IPW * 8, vb);
-  for (int kt = kt0; kt < kt1; kt += 2) {
-    k_step<S>(acc, b_rows_bytes, a_lds0, b_lds0, a_lds1, b_lds1, Ab, Wb, a_rows_bytes, kt, kt + 1 < kt1, wave, va,
-              vb, fa, fb);
-    if (kt + 1 < kt1)
-      k_step<S>(acc, b_rows_bytes, a_lds1, b_lds1, a_lds0, b_lds0, Ab, Wb, a_rows_bytes, kt + 1, kt + 2 < kt1, wave,
-                va, vb, fa, fb);
-  }
+  if (!wm) phase_barrier();
+  wait_vm<0>();
+  __syncthreads();  // no copy in flight, every wave is done with the regions
 
   // ---- epilogue -------------------------------------------------------------------
-  // every wave is done reading the tiles and no copy is in flight: the four
-  // tile buffers become staging space, STAGE_B bytes per wave (fp32 rows of
-  // 256 B, 16-byte chunks XOR-swizzled by row), PASS_ROWS rows per pass
-  __syncthreads();
-  // wave w's region: bytes [w STAGE_B, (w+1) STAGE_B) of a_lds0 | b_lds0 |
-  // a_lds1 | b_lds1 taken in this order (a region never straddles two)
-  auto stage_of = [&](int w) -> unsigned char * {
-    const int off = w * S::STAGE_B;
-    constexpr int A = S::ATILE, B = S::BTILE;
-    return off < A ? a_lds0 + off : off < A + B ? b_lds0 + (off - A) : off < 2 * A + B ? a_lds1 + (off - A - B)
-                                                                                       : b_lds1 + (off - 2 * A - B);
-  };
-  unsigned char *stg = stage_of(wave);
-  constexpr int WAVES_N = S::TN / S::WN;
-  // GLU: the gate waves (wn < WAVES_N / 2) finish the rows; their partner
-  // holds the up block of the same output columns
-  const bool finisher = !GLU || wn < WAVES_N / 2;
-  const unsigned char *stg_up = GLU ? stage_of(wave + S::WAVES_M * (WAVES_N / 2)) : stg;
-  const int cg = lane & 7;
-  const int n = n0 + wn * S::WN + cg * 8;
+  // Each wave stages its 64 rows of a row half in fp32 in a region of its own
+  // (rows of 256 B, gated 128 B, 16-byte chunks XOR-swizzled by row), then
+  // each lane finishes 8 consecutive columns of a row, so that residual loads
+  // and stores are 16 bytes of whole row segments.
+  unsigned char *stg = L.r[0];
+#pragma unroll
+  for (int w = 1; w < 8; ++w) stg = wave == w ? L.r[w] : stg;
+  constexpr int CPR = GLU ? 4 : 8;        // lanes (8 columns each) per row
+  const int cg = lane % CPR;
+  const int n = n0 + wn * (TN / 4) + cg * 8;
+  const bool n_ok = n < N;
   float bias[8];
   {
     bf16x8 bv = bf16x8{};
-    if (!GLU && !PARTIAL && p.bias) bv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.bias) + n);
+    if (!GLU && S.bias && k_parts == 1 && n_ok) bv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(S.bias) + n);
 #pragma unroll
     for (int e = 0; e < 8; ++e) bias[e] = (float)bv[e];
   }
+  // every residual piece before the first store (C may be the residual, so the
+  // compiler cannot move a load over a store: a round trip each otherwise)
+  bf16x8 res[H][CPR];
 #pragma unroll
-  for (int pass = 0; pass < S::WM / S::PASS_ROWS; ++pass) {
+  for (int h = 0; h < H; ++h)
 #pragma unroll
-    for (int mb = 0; mb < S::MB; ++mb) {
-      if (mb * 32 / S::PASS_ROWS != pass && S::PASS_ROWS >= 32) continue;
+    for (int it = 0; it < CPR; ++it) {
+      const int64_t m = m0 + h * 128 + wm * 64 + it * (64 / CPR) + lane / CPR;
+      res[h][it] = bf16x8{};
+      if (!GLU && p.j.residual && k_parts == 1 && m < p.j.M && n_ok)
+        res[h][it] = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.j.residual) + m * N + n);
+    }
 #pragma unroll
-      for (int nb = 0; nb < S::NB; ++nb)
+  for (int h = 0; h < H; ++h) {
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const int row = mb * 32 + l32 - pass * S::PASS_ROWS;
-          const int c = nb * 8 + 2 * q + half;  // 4-column chunk of the wave's 64 columns
+    for (int mb = 0; mb < 4; ++mb) {
+      const int row = mb * 16 + l16;
+      if (GLU) {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb) {
           f32x4 v;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) v[e] = acc[mb][nb][4 * q + e];
-          *reinterpret_cast<f32x4 *>(stg + row * 256 + ((c ^ (row & 15)) << 4)) = v;
+          for (int e = 0; e < 4; ++e) {
+            const float g = s.acc[h][0][mb][nb][e];
+            v[e] = g / (1.0f + __expf(-g)) * s.acc[h][1][mb][nb][e];
+          }
+          *reinterpret_cast<f32x4 *>(stg + row * 128 + (((nb * 4 + quad) ^ ((row >> 1) & 7)) << 4)) = v;
         }
-    }
-    if (GLU) __syncthreads();  // the partner's up block is staged
-    // each lane then finishes 8 consecutive columns of one row: 8 rows per round
+      } else {
 #pragma unroll
-    for (int it = 0; it < S::PASS_ROWS / 8; ++it) {
-      if (!finisher) break;
-      const int row = it * 8 + (lane >> 3);
-      const int64_t m = m0 + wm * S::WM + pass * S::PASS_ROWS + row;
-      const f32x4 v0 = *reinterpret_cast<const f32x4 *>(stg + row * 256 + (((2 * cg) ^ (row & 15)) << 4));
-      const f32x4 v1 = *reinterpret_cast<const f32x4 *>(stg + row * 256 + (((2 * cg + 1) ^ (row & 15)) << 4));
-      if (PARTIAL) {
-        // the piece's fp32 sums: [TM][TN] per (tail tile, piece)
-        if (m < p.M) {
-          float *dst = p.part + ((size_t)(t - p.t_begin) * p.k_parts + kp) * (S::TM * S::TN) +
-                       (size_t)(m - m0) * S::TN + (n - n0);
-          *reinterpret_cast<f32x4 *>(dst) = v0;
-          *reinterpret_cast<f32x4 *>(dst + 4) = v1;
-        }
+        for (int j = 0; j < 2; ++j)
+#pragma unroll
+          for (int nb = 0; nb < 2; ++nb)
+            *reinterpret_cast<f32x4 *>(stg + row * 256 + (((j * 8 + nb * 4 + quad) ^ l16) << 4)) = s.acc[h][j][mb][nb];
+      }
+    }
+#pragma unroll
+    for (int it = 0; it < CPR; ++it) {
+      const int row = it * (64 / CPR) + lane / CPR;
+      const int64_t m = m0 + h * 128 + wm * 64 + row;
+      f32x4 v0, v1;
+      if (GLU) {
+        v0 = *reinterpret_cast<const f32x4 *>(stg + row * 128 + (((2 * cg) ^ ((row >> 1) & 7)) << 4));
+        v1 = *reinterpret_cast<const f32x4 *>(stg + row * 128 + (((2 * cg + 1) ^ ((row >> 1) & 7)) << 4));
+      } else {
+        v0 = *reinterpret_cast<const f32x4 *>(stg + row * 256 + (((2 * cg) ^ (row & 15)) << 4));
+        v1 = *reinterpret_cast<const f32x4 *>(stg + row * 256 + (((2 * cg + 1) ^ (row & 15)) << 4));
+      }
+      if (m >= p.j.M || !n_ok) continue;
+      if (H == 1 && k_parts > 1) {
+        float *dst = p.part + ((size_t)unit * k_parts + kp) * (128 * 256) + (size_t)(m - m0) * 256 + (n - n0);
+        *reinterpret_cast<f32x4 *>(dst) = v0;
+        *reinterpret_cast<f32x4 *>(dst + 4) = v1;
         continue;
       }
-      if (m < p.M) {
-        float o[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
-        if (GLU) {
-          const f32x4 u0 = *reinterpret_cast<const f32x4 *>(stg_up + row * 256 + (((2 * cg) ^ (row & 15)) << 4));
-          const f32x4 u1 =
-              *reinterpret_cast<const f32x4 *>(stg_up + row * 256 + (((2 * cg + 1) ^ (row & 15)) << 4));
-          const float u[8] = {u0[0], u0[1], u0[2], u0[3], u1[0], u1[1], u1[2], u1[3]};
+      float o[8] = {v0[0], v0[1], v0[2], v0[3], v1[0], v1[1], v1[2], v1[3]};
+      if (!GLU) {
 #pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] = o[e] / (1.0f + __expf(-o[e])) * u[e];
-        }
-        if (p.residual) {
-          const bf16x8 rv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.residual) + m * p.N + n);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) o[e] += (float)rv[e];
-        }
-        bf16x8 out;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) out[e] = (__bf16)(o[e] + bias[e]);
-        *reinterpret_cast<bf16x8 *>(static_cast<__bf16 *>(p.C) + m * p.N + n) = out;
+        for (int e = 0; e < 8; ++e) o[e] += (float)res[h][it][e];
       }
+      bf16x8 out;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) out[e] = (__bf16)(o[e] + bias[e]);
+      *reinterpret_cast<bf16x8 *>(static_cast<__bf16 *>(S.C) + m * N + n) = out;
     }
-    if (GLU) __syncthreads();  // the next pass restages over these rows
   }
 }
 
-// The tail tiles' k pieces summed: C = sum of pieces (+ residual) (+ bias), in
+// 256-row tile t of the tile order: groups of kGroupM M-tiles sweep the
+// column tiles.
+__device__ __forceinline__ void tile_coords(const GemmPlan &p, int t, int &tm, int &tc) {
+  const int span = kGroupM * p.tn;
+  const int first_m = (t / span) * kGroupM;
+  const int gsize = min(p.tiles_m - first_m, kGroupM);
+  tm = first_m + (t % span) % gsize;
+  tc = (t % span) / gsize;
+}
+// 128-row unit u: the halves of the cut tiles, then the last rows.
+__device__ __forceinline__ void unit_coords(const GemmPlan &p, int u, int64_t &m0, int &tc) {
+  if (u < 2 * p.n_cut) {
+    int tm;
+    tile_coords(p, p.n_full + u / 2, tm, tc);
+    m0 = (int64_t)tm * 256 + (u & 1) * 128;
+  } else {
+    tc = u - 2 * p.n_cut;
+    m0 = (int64_t)p.tiles_m * 256;
+  }
+}
+
+// Workgroup i runs on XCD i mod 8: the whole tiles, and after them the units
+// (piece-major), are cut into 8 contiguous ranges, one per XCD, so that
+// neighbours in the order share A and W rows in that XCD's L2.
+template <bool GLU>
+__global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(const GemmPlan p) {
+  // nine objects, so that the compiler can tell the copies in flight from the
+  // regions being read
+  __shared__ __attribute__((aligned(1024))) unsigned char r0[kRegion], r1[kRegion], r2[kRegion], r3[kRegion],
+      r4[kRegion], r5[kRegion], r6[kRegion], r7[kRegion], r8[kRegion];
+  const Lds L = {{r0, r1, r2, r3, r4, r5, r6, r7, r8}};
+  const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
+  const int full_per = (p.n_full + kXcds - 1) / kXcds;
+  if (slot < full_per) {
+    const int t = xcd * full_per + slot;
+    if (t >= p.n_full) return;
+    int tm, tc;
+    tile_coords(p, t, tm, tc);
+    run_tile<2, GLU>(p, (int64_t)tm * 256, tc, 0, 0, 1, L);
+    return;
+  }
+  const int jobs = p.n_half * p.k_parts, per = (jobs + kXcds - 1) / kXcds;
+  const int i = xcd * per + slot - full_per;
+  if (slot - full_per >= per || i >= jobs) return;
+  const int u = i % p.n_half;
+  int tc;
+  int64_t m0;
+  unit_coords(p, u, m0, tc);
+  run_tile<1, GLU>(p, m0, tc, u, i / p.n_half, p.k_parts, L);
+}
+
+// The cut units' k pieces summed: C = sum of pieces (+ residual) (+ bias), in
 // the order of the whole-tile epilogue. One thread per 8 columns of a row.
-template <class S>
-__global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmArgs p) {
-  constexpr int CHUNKS = S::TN / 8;
+__global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmPlan p) {
   const int64_t gid = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  const int64_t per_tile = (int64_t)S::TM * CHUNKS;
-  if (gid >= per_tile * p.t_count) return;
-  const int tl = (int)(gid / per_tile);
-  const int row = (int)(gid % per_tile) / CHUNKS, cg = (int)(gid % per_tile) % CHUNKS;
-  int tm, tn;
-  tile_coords(p, p.t_begin + tl, tm, tn);
-  const int64_t m = (int64_t)tm * S::TM + row;
-  if (m >= p.M) return;
-  const int n = tn * S::TN + cg * 8;
+  const int u = (int)(gid >> 12), row = (int)(gid >> 5) & 127, cg = (int)gid & 31;
+  if (u >= p.n_half) return;
+  int tc;
+  int64_t m0;
+  unit_coords(p, u, m0, tc);
+  int si = 0;
+  while (si + 1 < p.j.n_segs && tc >= p.seg_tn[si]) tc -= p.seg_tn[si++];
+  const GemmSeg &S = p.j.seg[si];
+  const int64_t m = m0 + row;
+  const int n = tc * 256 + cg * 8;
+  if (m >= p.j.M || n >= S.N) return;
   float o[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-  const float *src = p.part + (size_t)tl * p.k_parts * (S::TM * S::TN) + (size_t)row * S::TN + cg * 8;
+  const float *src = p.part + (size_t)u * p.k_parts * (128 * 256) + (size_t)row * 256 + cg * 8;
   for (int k = 0; k < p.k_parts; ++k) {
-    const f32x4 a = *reinterpret_cast<const f32x4 *>(src + (size_t)k * (S::TM * S::TN));
-    const f32x4 b = *reinterpret_cast<const f32x4 *>(src + (size_t)k * (S::TM * S::TN) + 4);
+    const f32x4 a = *reinterpret_cast<const f32x4 *>(src + (size_t)k * (128 * 256));
+    const f32x4 b = *reinterpret_cast<const f32x4 *>(src + (size_t)k * (128 * 256) + 4);
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
       o[e] += a[e];
       o[4 + e] += b[e];
     }
   }
-  if (p.residual) {
-    const bf16x8 rv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.residual) + m * p.N + n);
+  if (p.j.residual) {
+    const bf16x8 rv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.j.residual) + m * S.N + n);
 #pragma unroll
     for (int e = 0; e < 8; ++e) o[e] += (float)rv[e];
   }
   bf16x8 bv = bf16x8{};
-  if (p.bias) bv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(p.bias) + n);
+  if (S.bias) bv = *reinterpret_cast<const bf16x8 *>(static_cast<const __bf16 *>(S.bias) + n);
   bf16x8 out;
 #pragma unroll
   for (int e = 0; e < 8; ++e) out[e] = (__bf16)(o[e] + (float)bv[e]);
-  *reinterpret_cast<bf16x8 *>(static_cast<__bf16 *>(p.C) + m * p.N + n) = out;
+  *reinterpret_cast<bf16x8 *>(static_cast<__bf16 *>(S.C) + m * S.N + n) = out;
 }
 
-using SmallTile = Shape<128, 128, 64, 64>;  // 4 waves, two workgroups per CU
-using LargeTile = Shape<256, 256, 128, 64>;  // 8 waves, one workgroup per CU
-
-template <class S>
-hipError_t launch_shape(GemmArgs p, hipStream_t st) {
-  p.tiles_m = (int)((p.M + S::TM - 1) / S::TM);
-  p.tiles_n = p.N / (p.glu ? S::TN / 2 : S::TN);
-  const int n_tiles = p.tiles_m * p.tiles_n;
-  if (n_tiles <= 0) return hipSuccess;
-  const int per_xcd = (n_tiles + kXcds - 1) / kXcds;
-  if (p.glu) gemm_bf16_kernel<S, true><<<dim3(kXcds * per_xcd), dim3(S::THREADS), 0, st>>>(p);
-  else gemm_bf16_kernel<S, false><<<dim3(kXcds * per_xcd), dim3(S::THREADS), 0, st>>>(p);
-  return hipGetLastError();
-}
-
-// Whole rounds of the resident workgroups as whole tiles, the remaining tiles
-// cut along k into pieces that fill the idle slots, then the reduction.
-template <class S>
-hipError_t launch_split(GemmArgs p, float *part, size_t part_bytes, hipStream_t st) {
-  constexpr int slots = S::THREADS == 256 ? 512 : 256;  // resident workgroups: 2 per CU for 4 waves, else 1
-  p.tiles_m = (int)((p.M + S::TM - 1) / S::TM);
-  p.tiles_n = p.N / S::TN;
-  const int n_tiles = p.tiles_m * p.tiles_n;
-  const int full = n_tiles / slots * slots, tail = n_tiles - full;
-  const int KT = p.K / kTK;
-  const int k_parts = tail > 0 ? std::min(std::min(slots / tail, KT / 4), 8) : 0;
-  if (n_tiles <= 0 || k_parts < 2 || (size_t)tail * k_parts * S::TM * S::TN * 4 > part_bytes)
-    return launch_shape<S>(p, st);
-  if (full > 0) {
-    GemmArgs a = p;
-    a.t_begin = 0;
-    a.t_count = full;
-    gemm_bf16_kernel<S, false><<<dim3(kXcds * ((full + kXcds - 1) / kXcds)), dim3(S::THREADS), 0, st>>>(a);
+// Which tiles run whole, as halves or in k pieces. Rows beyond the last whole
+// 256-row tile take one more 256-row tile if there are more than 128 of them,
+// else 128-row units. Whole rounds of 256 tiles always run whole; the r tiles
+// of a last, partial round run
+//   whole, r + units workgroups:                one tile's time,
+//   as 2 r halves if these fit the CUs:         0.57 of it (a k step of a
+//     128-row tile takes 0.55-0.57 us, of a 256-row tile 0.95-1.0 us while
+//     part of the CUs is busy; K = 18944: 160 against 280 us),
+//   as halves cut into P pieces along k:        1/P of that, plus the fp32
+//     pieces written and read back (128 KiB each, at ~4.5 TB/s for both
+//     passes) and the reduction's launch,
+// whichever the figures below say is shortest.
+void plan_job(GemmPlan &p, size_t part_bytes) {
+  const GemmJob &j = p.j;
+  const int tn_out = j.glu ? 128 : 256;
+  p.tn = 0;
+  for (int i = 0; i < j.n_segs; ++i) {
+    p.seg_tn[i] = (j.seg[i].N + tn_out - 1) / tn_out;
+    p.tn += p.seg_tn[i];
   }
-  GemmArgs b = p;
-  b.t_begin = full;
-  b.t_count = tail;
-  b.k_parts = k_parts;
-  b.part = part;
-  gemm_bf16_kernel<S, false, true><<<dim3(tail * k_parts), dim3(S::THREADS), 0, st>>>(b);
-  const int64_t threads = (int64_t)tail * S::TM * (S::TN / 8);
-  gemm_reduce_kernel<S><<<dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, st>>>(b);
-  return hipGetLastError();
-}
-
-bool use_large(const GemmArgs &a) {
-  // the large tile needs whole output tiles (256 columns, 128 gated) and
-  // enough tiles to fill the CUs
-  const int out_tn = a.glu ? LargeTile::TN / 2 : LargeTile::TN;
-  const int64_t large_tiles = ((a.M + LargeTile::TM - 1) / LargeTile::TM) * (a.N / out_tn);
-  return a.N % out_tn == 0 && large_tiles >= 2 * 256;
+  const int rest = (int)(j.M % 256);
+  p.tiles_m = (int)(j.M / 256) + (rest > 128 ? 1 : 0);
+  const int edge = rest > 0 && rest <= 128 ? p.tn : 0;  // 128-row units of the last rows
+  const int n_tiles = p.tiles_m * p.tn, r = n_tiles % kCus;
+  const double kt = j.K / kTK;
+  const double whole_us = 0.97 * kt + 8.0;
+  auto half_us = [&](double k) { return 0.57 * k + 6.0; };
+  p.n_cut = 0;
+  p.k_parts = 1;
+  const int units = 2 * r + edge;
+  double best = r ? whole_us + (r + edge > kCus ? half_us(kt) : 0.0) : half_us(kt) * ((edge + kCus - 1) / kCus);
+  if (units > 0 && units <= kCus) {
+    for (int parts = 1; parts * units <= kCus && (parts == 1 || 2 * parts <= kt); ++parts) {
+      if (parts > 1 && (p.part == nullptr || j.glu || (size_t)units * parts * 128 * 256 * 4 > part_bytes)) break;
+      const double us = half_us(kt / parts) + (parts > 1 ? 5.0 + units * parts * 0.058 : 0.0);
+      if (us < best) {
+        best = us;
+        p.n_cut = r;
+        p.k_parts = parts;
+      }
+    }
+  }
+  p.n_full = n_tiles - p.n_cut;
+  p.n_half = 2 * p.n_cut + edge;
 }
 
 }  // namespace
 
-hipError_t launch_gemm_split(const GemmArgs &a, float *part, size_t part_bytes, hipStream_t st) {
-  if (a.glu || part == nullptr) return launch_gemm(a, st);
-  return use_large(a) ? launch_split<LargeTile>(a, part, part_bytes, st)
-                      : launch_split<SmallTile>(a, part, part_bytes, st);
-}
-
-hipError_t launch_gemm(const GemmArgs &a, hipStream_t st) {
-  return use_large(a) ? launch_shape<LargeTile>(a, st) : launch_shape<SmallTile>(a, st);
+hipError_t launch_gemm_job(const GemmJob &job, float *part, size_t part_bytes, hipStream_t st) {
+  GemmPlan p{};
+  p.j = job;
+  p.part = part;
+  if (job.M <= 0 || job.n_segs <= 0) return hipSuccess;
+  plan_job(p, part_bytes);
+  const int blocks = kXcds * ((p.n_full + kXcds - 1) / kXcds + (p.n_half * p.k_parts + kXcds - 1) / kXcds);
+  if (job.glu) gemm_bf16_kernel<true><<<dim3(blocks), dim3(512), 0, st>>>(p);
+  else gemm_bf16_kernel<false><<<dim3(blocks), dim3(512), 0, st>>>(p);
+  if (p.k_parts > 1) gemm_reduce_kernel<<<dim3(p.n_half * 16), dim3(256), 0, st>>>(p);
+  return hipGetLastError();
 }
 
 }  // namespace daf
