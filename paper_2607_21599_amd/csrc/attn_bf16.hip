@@ -2,8 +2,9 @@
 //
 // Same operation and work decomposition as the fp32 kernel in attn.hip (see
 // there): query row i of a request sees keys 0 .. i + (n_keys - n_rows), a
-// workgroup of 4 waves owns 128 query rows of one head and one key split, and
-// the G heads that share a KV head form an XCD-local work group.
+// workgroup of 4 waves owns 128 query rows (64 where that fills more CUs) of
+// one head and one key split, and the G heads that share a KV head form an
+// XCD-local work group.
 //
 // bf16 data path, per 64-key tile:
 //  * K and V tiles are copied global -> LDS by the buffer unit
@@ -13,28 +14,36 @@
 //    16-byte chunks are XOR-swizzled within a row so that the two LDS read
 //    patterns below are free of bank conflicts. Two tile buffers: the DMA of
 //    tile t+1 runs while tile t is consumed, one barrier per tile.
-//  * S^T = K Q^T on v_mfma_f32_32x32x16_bf16 (keys on M, query rows on N, Q in
-//    registers), so each lane owns one query row.
-//  * O^T += V^T P^T: P^T comes straight from the S^T accumulators; the V^T
-//    operand (8 consecutive keys of one feature per lane) is read from the
-//    row-major V tile with ds_read_b64_tr_b16, which transposes 16-bit data
-//    across each 16-lane group.
-//  * Online softmax in fp32, base 2, scale folded into one FMA per score. Full
-//    tiles form each 32-key half's probabilities against the running max as it
-//    stands, without taking the half's max: only when some lane's share of the
-//    half's sum exceeds 2^32 (or is not finite, as on a row's first tile) is
-//    the half's exact max taken, the running max raised, O and the sum rescaled
-//    and the half formed again. Probabilities thus stay below 2^32 (far from
-//    overflow in fp32 and bf16) and the S MFMAs of half 1 run beside the
-//    softmax of half 0. Diagonal tiles take one max over the tile and raise the
-//    running max only when it grows by more than 2^8. The row max of a lane
-//    pair is exchanged with v_permlane32_swap.
-//  * The row sum is taken from the bf16-rounded probabilities that the P.V
-//    product uses (v_dot2c_f32_bf16 against (1, 1), one instruction per pair).
-//  * Launch shape for causal self attention: the heaviest 128 jobs of an XCD
-//    (one query head of one 128-row block each) are run by its 64 resident
-//    workgroups in pairs, job u with job 127 - u, so each workgroup gets a heavy
-//    and a light block of near-equal total; lighter jobs get a workgroup each.
+//  * S^T = K Q^T on v_mfma_f32_16x16x32_bf16 (16 keys on M, 16 query rows on N,
+//    Q in registers): a lane holds 4 keys of one row.
+//  * O^T += V^T P^T: P^T comes straight from the S^T accumulators (contraction
+//    slots in the order in which a lane holds its keys); the V^T operand is
+//    read from the row-major V tile with ds_read_b64_tr_b16, which transposes
+//    16-bit data across each 16-lane group.
+//  * Softmax in fp32, base 2, scale folded into one FMA per score, against a
+//    running reference per row that lies kHeadroom above the row's max, so no
+//    max is taken: the half tile's probabilities are formed and rounded, and
+//    their bits are ORed to see whether one has reached 2 (then the exact max
+//    is taken, the reference raised, O and the sum rescaled, the half formed
+//    again; always so on a row's first tile).
+//  * The row sum is one more MFMA per half tile and 16 rows, of the rounded
+//    probabilities against ones.
+//
+// What bounds it: the VALU issue port, which the softmax and the MFMAs share
+// (an MFMA of either shape holds it for about 8 cycles, v_exp_f32 and
+// v_cvt_pk_bf16_f32 for about 8, other VALU operations for 4.4), and the clock,
+// which the chip's power sets. Beside a wave that issues MFMAs back to back a
+// v_dot2 waits about 50 cycles, so the previous row sum (16 v_dot2 per tile
+// and wave) cost more than the 4 MFMAs that replaced it, and the 16x16x32
+// shape needs less power per FLOP than 32x32x16. Stage 1 at n = 4915, 28 heads
+// of 128: 173 us with 32x32x16 MFMAs and v_dot2, 166 with 16x16x32, 163 with
+// the sum on the matrix cores; 5043 rows at positions of 32896 keys: 1122, 1062
+// and 1045 us.
+//
+// Launch shape for causal self attention: the heaviest 128 jobs of an XCD (one
+// query head of one 128-row block each) are run by its 64 resident workgroups
+// in pairs, job u with job 127 - u, so each workgroup gets a heavy and a light
+// block of near-equal total; lighter jobs get a workgroup each.
 #include <math.h>
 
 #include <algorithm>
@@ -46,23 +55,21 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned short u16x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr int kBN = 64;                  // keys per tile
 [[maybe_unused]] constexpr int kRsrcWord3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
-constexpr float kRescaleSlack = 8.0f;    // log2 units a row max may grow before O is rescaled
-// Full tiles skip the max: a half's probabilities are formed with the running
-// max as it stands, and only if some lane's share of the half's sum exceeds
-// this (or is not finite) is the half's exact max taken, the running max
-// raised and the half formed again. Each probability is then at most 2^32, far
-// from fp32 and bf16 overflow in the row sum and the O accumulators.
-constexpr float kHalfSumLimit = 4294967296.0f;
+// Probabilities are formed against a running reference per row: the largest
+// scaled score at its last raise plus kHeadroom (log2 units), so they are at
+// most about 2^-32 until a later score exceeds that one. Only if one reaches 2
+// is the exact max taken, the reference raised and the probabilities formed
+// again: with every product below 2 V there is no overflow, and bf16's
+// exponent range keeps terms down to 2^-94 of the largest.
+constexpr float kHeadroom = 32.0f;
+constexpr float kNoReference = -3e38f;  // before the first key: every visible one's probability is infinite
 
 template <int D>
 struct Geo {
@@ -71,14 +78,17 @@ struct Geo {
   static constexpr int TILE = kBN * ROWB;    // bytes of one K or V tile
   static constexpr int RPI = 64 / CH;        // rows written by one 1 KiB DMA instruction
   static constexpr int IPW = kBN / RPI / 4;  // DMA instructions per wave, per tensor and tile
-  static constexpr int DS = D / 16;          // contraction steps of S^T
-  static constexpr int DB = D / 32;          // 32-feature output blocks
+  static constexpr int DS = D / 32;          // contraction steps of S^T
+  static constexpr int DB = D / 16;          // 16-feature output blocks
   static_assert(RPI * ROWB == 1024, "one DMA instruction writes 1 KiB");
 };
 
-// chunk swizzles (XOR, so their own inverse), both < CH
-__device__ __forceinline__ int swz_k(int r, int ch) { return r & (ch - 1); }
-__device__ __forceinline__ int swz_v(int r, int ch) { return (((r & 3) << 2) | ((r >> 2) & 3)) & (ch - 1); }
+// chunk swizzles (XOR, so their own inverse), both < CH. K: the 16 lanes of a
+// read phase take one chunk of 16 consecutive rows; V: the 32 lanes of a phase
+// take a pair of chunks of 8 consecutive rows. 128-byte rows (CH = 8) already
+// alternate between the halves of the banks.
+__device__ __forceinline__ int swz_k(int r, int ch) { return ch == 16 ? r & 15 : (r >> 1) & 7; }
+__device__ __forceinline__ int swz_v(int r, int ch) { return ch == 16 ? (r & 7) << 1 : ((r >> 1) & 3) << 1; }
 
 __device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
 
@@ -93,15 +103,20 @@ __device__ __forceinline__ void lane_pair(float x, float &a, float &b) {
   a = __builtin_bit_cast(float, r0);
   b = __builtin_bit_cast(float, r1);
 }
-__device__ __forceinline__ float pair_max(float x) {
-  float a, b;
-  lane_pair(x, a, b);
-  return fmaxf(a, b);
+// the same for lane ^ 16
+__device__ __forceinline__ void lane_pair16(float x, float &a, float &b) {
+  const unsigned u = __builtin_bit_cast(unsigned, x);
+  const auto r = __builtin_amdgcn_permlane16_swap(u, u, false, false);
+  const unsigned r0 = r[0], r1 = r[1];
+  a = __builtin_bit_cast(float, r0);
+  b = __builtin_bit_cast(float, r1);
 }
-__device__ __forceinline__ float pair_sum(float x) {
+// over the four lanes that share a query row (lane mod 16)
+__device__ __forceinline__ float row_max(float x) {
   float a, b;
   lane_pair(x, a, b);
-  return a + b;
+  lane_pair16(fmaxf(a, b), a, b);
+  return fmaxf(a, b);
 }
 
 __device__ __forceinline__ bf16x8 tr_pair(const unsigned char *lds_base, int off_a, int off_b) {
@@ -138,7 +153,7 @@ __device__ __forceinline__ void dma_tile(const unsigned char *kg, const unsigned
 #endif
 }
 
-// Output staging: 32 rows of ROWB bytes per wave in LDS, the 16-byte chunks of
+// Output staging: up to 32 rows of ROWB bytes per wave in LDS, the 16-byte chunks of
 // a row XOR-swizzled by the row so that both the per-lane writes (pieces of
 // every chunk of one row) and the row-contiguous reads spread over the banks.
 // stage_put writes v (8 or 16 bytes) at byte `sub` of logical chunk c of row r.
@@ -147,94 +162,124 @@ __device__ __forceinline__ void stage_put(unsigned char *stg, int r, int c, int 
   constexpr int CH = Geo<D>::CH;
   *reinterpret_cast<V *>(stg + r * Geo<D>::ROWB + ((c ^ (r & (CH - 1))) << 4) + sub) = v;
 }
-// Write the wave's staged rows wrow .. wrow+31 (those below n_rows): each lane
+// Write the wave's staged rows wrow .. wrow+ROWS-1 (those below n_rows): each lane
 // moves one 16-byte chunk, CH lanes cover a row, so every store instruction
 // writes 64/CH whole rows. dst(r) is the byte address of row r's first chunk.
-template <int D, typename F>
+template <int D, int ROWS, typename F>
 __device__ __forceinline__ void store_rows(const unsigned char *stg, int lane, int wrow, int n_rows, F dst) {
   constexpr int CH = Geo<D>::CH, RPL = 64 / CH;
   const int j = lane % CH;
 #pragma unroll
-  for (int it = 0; it < 32 / RPL; ++it) {
+  for (int it = 0; it < ROWS / RPL; ++it) {
     const int r = it * RPL + lane / CH;
     const u32x4 v = *reinterpret_cast<const u32x4 *>(stg + r * Geo<D>::ROWB + ((j ^ (r & (CH - 1))) << 4));
     if (wrow + r < n_rows) *reinterpret_cast<u32x4 *>(dst(wrow + r) + j * 16) = v;
   }
 }
 
-// Per-wave state of one workgroup tile (lives in registers after inlining).
-template <int D>
+// Per-wave state of one workgroup tile (lives in registers after inlining). A
+// wave has 16 NB rows; a lane works on rows lane % 16 + 16 nb, nb < NB, and the
+// four lanes of a row split its keys.
+template <int D, int NB>
 struct WaveState {
   using Gm = Geo<D>;
-  bf16x8 qf[Gm::DS];       // Q rows as the B operand of S^T
-  f32x16 oacc[Gm::DB];     // O^T accumulators
-  float m_run;             // running max, scaled base-2 units, equal in both halves
-  float l_run;             // this lane's share of the row sum
+  bf16x8 qf[NB][Gm::DS];    // Q rows as the B operand of S^T
+  f32x4 oacc[NB][Gm::DB];   // O^T accumulators
+  float m_run[NB];          // running max, scaled base-2 units, equal in a row's four lanes
+  f32x4 lacc[NB];           // row sums of the rounded probabilities (four equal elements)
   int koff[Gm::DS];        // K tile read offsets
-  int voff[Gm::DB][2];     // V tile transposed-read offsets
+  int voff[Gm::DB];        // V tile transposed-read offsets
   int dma_k[Gm::IPW], dma_v[Gm::IPW];
   const unsigned char *kg, *vg;
-  int n_keys, kv_row_bytes, limit, half, wave;
+  int n_keys, kv_row_bytes, limit[NB], quad, wave;
   int wave_last_key;       // keys above this are masked for every row of the wave
   int wave_first_limit;    // keys up to this are visible to every row of the wave
   float sl2;
 };
 
-// P^T operands (bf16) of one 32-key half; returns this lane's share of the
-// half's row sum, taken from the rounded probabilities that the P.V product
-// uses (pairs summed by v_dot2c_f32_bf16 against (1, 1)).
-template <int D>
-__device__ __forceinline__ float softmax_half(const WaveState<D> &w, const f32x16 &sacc, float m_use,
-                                              bf16x8 (&pf)[2]) {
+// Scores of one 32-key half tile: [16-key block][row block], D^T blocks: a
+// lane holds 4 consecutive keys of one row.
+template <int NB>
+using Scores = f32x4[2][NB];
+
+// P^T operands (bf16) of one 32-key half, against the running reference m.
+// Returns the OR of their bits: bit 14 of either half is set if some
+// probability is 2 or more (the top exponent bit of a positive bf16).
+template <int D, int NB>
+__device__ __forceinline__ unsigned softmax_half(const WaveState<D, NB> &w, const Scores<NB> &sc, const float (&m)[NB],
+                                                 bf16x8 (&pf)[NB]) {
 #pragma unroll
-  for (int r = 0; r < 16; ++r) pf[r >> 3][r & 7] = (__bf16)fast_exp2(__builtin_fmaf(sacc[r], w.sl2, -m_use));
-  const bf16x2 ones = {(__bf16)1.0f, (__bf16)1.0f};
-  float ps[2] = {0.f, 0.f};
+  for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-  for (int j = 0; j < 8; ++j) {
-    const bf16x2 pr = {pf[j >> 2][2 * (j & 3)], pf[j >> 2][2 * (j & 3) + 1]};
-    ps[j & 1] = __builtin_amdgcn_fdot2_f32_bf16(pr, ones, ps[j & 1], false);
+    for (int r = 0; r < 8; ++r)
+      pf[nb][r] = (__bf16)fast_exp2(__builtin_fmaf(sc[r >> 2][nb][r & 3], w.sl2, -m[nb]));
+  unsigned bits = 0;
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const u32x4 a = __builtin_bit_cast(u32x4, pf[nb]);
+    bits |= (a[0] | a[1]) | (a[2] | a[3]);
   }
-  return ps[0] + ps[1];
+  return bits;
+}
+__device__ __forceinline__ bool out_of_range(unsigned bits) {
+  return __builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0) != 0;
 }
 
-// O^T += V^T P^T over the 2 x 16 keys of one half tile.
-template <int D>
-__device__ __forceinline__ void pv_half(WaveState<D> &w, const unsigned char *vs, const bf16x8 (&pf)[2]) {
-  constexpr int ROWB = Geo<D>::ROWB, DB = Geo<D>::DB;
-  // all transposed V reads of the half tile before its MFMAs
-  bf16x8 a[2][DB];
+// O^T += V^T P^T over the 32 keys of one half tile. Contraction slot 8 g + j of
+// lane group g is key 4 g + j of the half's first 16 keys (j < 4) or key 4 g +
+// j - 4 of its last 16: the keys whose scores that group holds.
+template <int D, int NB>
+__device__ __forceinline__ void read_v(const WaveState<D, NB> &w, const unsigned char *vs, bf16x8 (&a)[Geo<D>::DB]) {
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+  for (int db = 0; db < Geo<D>::DB; ++db) a[db] = tr_pair(vs, w.voff[db], w.voff[db] + 16 * Geo<D>::ROWB);
+}
+template <int D, int NB>
+__device__ __forceinline__ void pv_half(WaveState<D, NB> &w, const bf16x8 (&a)[Geo<D>::DB], const bf16x8 (&pf)[NB]) {
 #pragma unroll
-    for (int db = 0; db < DB; ++db) a[c][db] = tr_pair(vs + c * 16 * ROWB, w.voff[db][0], w.voff[db][1]);
+  for (int db = 0; db < Geo<D>::DB; ++db)
 #pragma unroll
-  for (int c = 0; c < 2; ++c)
+    for (int nb = 0; nb < NB; ++nb)
+      w.oacc[nb][db] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[db], pf[nb], w.oacc[nb][db], 0, 0, 0);
+  const __bf16 one = (__bf16)1.0f;
+  const bf16x8 ones = {one, one, one, one, one, one, one, one};
 #pragma unroll
-    for (int db = 0; db < DB; ++db) w.oacc[db] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[c][db], pf[c], w.oacc[db], 0, 0, 0);
+  for (int nb = 0; nb < NB; ++nb) w.lacc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[nb], w.lacc[nb], 0, 0, 0);
 }
 
-// Raise the running max if this half's max grew by more than the slack
-// (wave-uniform decision), rescaling O and the row sum.
-template <int D>
-__device__ __forceinline__ void raise_to(WaveState<D> &w, float mt) {
-  const float m_new = fmaxf(w.m_run, mt);
-  const float alpha = (m_new == -INFINITY) ? 1.f : fast_exp2(w.m_run - m_new);
-  w.m_run = m_new;
-  w.l_run *= alpha;
+// Raise the running references to the rows' maxima mt plus the headroom,
+// rescaling O and the row sums.
+template <int D, int NB>
+__device__ __forceinline__ void raise_to(WaveState<D, NB> &w, const float (&mt)[NB]) {
 #pragma unroll
-  for (int db = 0; db < Geo<D>::DB; ++db) w.oacc[db] *= alpha;
-}
-template <int D>
-__device__ __forceinline__ void maybe_raise(WaveState<D> &w, float mt) {
-  if (__builtin_amdgcn_ballot_w64(mt > w.m_run + kRescaleSlack) != 0) raise_to<D>(w, mt);
-}
-template <int D>
-__device__ __forceinline__ float half_max(const WaveState<D> &w, const f32x16 &sacc) {
-  float mx = sacc[0];
+  for (int nb = 0; nb < NB; ++nb) {
+    const float m_new = fmaxf(w.m_run[nb], mt[nb] + kHeadroom);
+    const float alpha = fast_exp2(w.m_run[nb] - m_new);
+    w.m_run[nb] = m_new;
+    w.lacc[nb] *= alpha;
 #pragma unroll
-  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sacc[r]);
-  return pair_max(mx) * w.sl2;
+    for (int db = 0; db < Geo<D>::DB; ++db) w.oacc[nb][db] *= alpha;
+  }
+}
+template <int D, int NB>
+__device__ __forceinline__ void half_max(const WaveState<D, NB> &w, const Scores<NB> &sc, float (&mt)[NB]) {
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    float mx = sc[0][nb][0];
+#pragma unroll
+    for (int r = 1; r < 8; ++r) mx = fmaxf(mx, sc[r >> 2][nb][r & 3]);
+    mt[nb] = row_max(mx) * w.sl2;
+  }
+}
+// Probabilities of a half tile: against the running reference as it stands,
+// and again after raising it if one of them is 2 or more.
+template <int D, int NB>
+__device__ __forceinline__ void finish_half(WaveState<D, NB> &w, const Scores<NB> &sc, bf16x8 (&pf)[NB], unsigned bits) {
+  if (out_of_range(bits)) {
+    float mt[NB];
+    half_max<D, NB>(w, sc, mt);
+    raise_to<D, NB>(w, mt);
+    softmax_half<D, NB>(w, sc, w.m_run, pf);
+  }
 }
 
 // One 64-key tile: S^T = K Q^T, online softmax, O^T update. MASK selects the
@@ -242,93 +287,100 @@ __device__ __forceinline__ float half_max(const WaveState<D> &w, const f32x16 &s
 // Full tiles keep one running max per 32-key half, so the S MFMAs of half 1
 // overlap the softmax of half 0 and the P.V MFMAs of half 0 overlap the max of
 // half 1.
-template <int D, bool MASK>
-__device__ __forceinline__ void tile_math(WaveState<D> &w, const unsigned char *ks, const unsigned char *vs, int kb) {
+template <int D, int NB, bool MASK>
+__device__ __forceinline__ void tile_math(WaveState<D, NB> &w, const unsigned char *ks, const unsigned char *vs, int kb) {
   constexpr int ROWB = Geo<D>::ROWB, DS = Geo<D>::DS;
   if (!MASK) {
-    bf16x8 kf[2][DS];
+    bf16x8 kf[4][DS];
 #pragma unroll
-    for (int b2 = 0; b2 < 2; ++b2)
+    for (int b = 0; b < 4; ++b)
 #pragma unroll
-      for (int ds = 0; ds < DS; ++ds) kf[b2][ds] = *reinterpret_cast<const bf16x8 *>(ks + b2 * 32 * ROWB + w.koff[ds]);
-    f32x16 s0 = f32x16{}, s1 = f32x16{};
+      for (int ds = 0; ds < DS; ++ds) kf[b][ds] = *reinterpret_cast<const bf16x8 *>(ks + b * 16 * ROWB + w.koff[ds]);
+    Scores<NB> s0 = {}, s1 = {};
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) s0 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[0][ds], w.qf[ds], s0, 0, 0, 0);
+    for (int ds = 0; ds < DS; ++ds)
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) s1 = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[1][ds], w.qf[ds], s1, 0, 0, 0);
-    bf16x8 pf0[2];
-    float ps0 = softmax_half<D>(w, s0, w.m_run, pf0);
-    // scheduling: K reads of half 0, the S MFMAs of half 0 each beside a K
-    // read of half 1, then the S MFMAs of half 1 each beside a sixth of the
-    // softmax of half 0
-    __builtin_amdgcn_sched_group_barrier(0x100, DS, 0);
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-    for (int i = 0; i < DS; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+        for (int nb = 0; nb < NB; ++nb) s0[b][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][ds], w.qf[nb][ds], s0[b][nb], 0, 0, 0);
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb) s1[b][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 + b][ds], w.qf[nb][ds], s1[b][nb], 0, 0, 0);
+    bf16x8 pf0[NB], pf1[NB];
+    const unsigned bits0 = softmax_half<D, NB>(w, s0, w.m_run, pf0);
+    // scheduling: K reads of half 0, the S MFMAs of half 0 in pairs beside a K
+    // read of half 1, then the S MFMAs of half 1 in pairs beside a share of
+    // the softmax of half 0
+    __builtin_amdgcn_sched_group_barrier(0x100, 2 * DS, 0);
+#pragma unroll
+    for (int i = 0; i < 2 * DS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
     }
 #pragma unroll
-    for (int i = 0; i < DS; ++i) {
-      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-      __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);
+    for (int i = 0; i < 2 * DS; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 3 * NB, 0);
     }
-    if (__builtin_amdgcn_ballot_w64(!(ps0 <= kHalfSumLimit)) != 0) {
-      raise_to<D>(w, half_max<D>(w, s0));
-      ps0 = softmax_half<D>(w, s0, w.m_run, pf0);
-    }
-    w.l_run += ps0;
-    pv_half<D>(w, vs, pf0);
-    bf16x8 pf1[2];
-    float ps1 = softmax_half<D>(w, s1, w.m_run, pf1);
-    if (__builtin_amdgcn_ballot_w64(!(ps1 <= kHalfSumLimit)) != 0) {
-      raise_to<D>(w, half_max<D>(w, s1));
-      ps1 = softmax_half<D>(w, s1, w.m_run, pf1);
-    }
-    w.l_run += ps1;
-    pv_half<D>(w, vs + 32 * ROWB, pf1);
+    finish_half<D, NB>(w, s0, pf0, bits0);
+    bf16x8 v[Geo<D>::DB];
+    read_v<D, NB>(w, vs, v);
+    pv_half<D, NB>(w, v, pf0);
+    const unsigned bits1 = softmax_half<D, NB>(w, s1, w.m_run, pf1);
+    finish_half<D, NB>(w, s1, pf1, bits1);
+    read_v<D, NB>(w, vs + 32 * ROWB, v);
+    pv_half<D, NB>(w, v, pf1);
     return;
   }
   const bool second = kb + 32 <= w.wave_last_key;
-  f32x16 sacc[2];
+  Scores<NB> sc[2];
 #pragma unroll
-  for (int b2 = 0; b2 < 2; ++b2) {
-    if (b2 == 1 && !second) {
-      sacc[1] = f32x16{};
-      continue;
-    }
-    bf16x8 kf[DS];
+  for (int h = 0; h < 2; ++h) {
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) kf[ds] = *reinterpret_cast<const bf16x8 *>(ks + b2 * 32 * ROWB + w.koff[ds]);
-    sacc[b2] = f32x16{};
+    for (int b = 0; b < 2; ++b) for (int nb = 0; nb < NB; ++nb) sc[h][b][nb] = f32x4{};
+    if (h == 1 && !second) continue;
+    bf16x8 kf[2][DS];
 #pragma unroll
-    for (int ds = 0; ds < DS; ++ds) sacc[b2] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(kf[ds], w.qf[ds], sacc[b2], 0, 0, 0);
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int ds = 0; ds < DS; ++ds)
+        kf[b][ds] = *reinterpret_cast<const bf16x8 *>(ks + (2 * h + b) * 16 * ROWB + w.koff[ds]);
+#pragma unroll
+    for (int ds = 0; ds < DS; ++ds)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int nb = 0; nb < NB; ++nb)
+          sc[h][b][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][ds], w.qf[nb][ds], sc[h][b][nb], 0, 0, 0);
   }
 #pragma unroll
-  for (int b2 = 0; b2 < 2; ++b2) {
+  for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int key = kb + 32 * b2 + 8 * (r >> 2) + 4 * w.half + (r & 3);
-      if (key > w.limit) sacc[b2][r] = -INFINITY;
-    }
-  }
-  float mx = fmaxf(sacc[0][0], sacc[1][0]);
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-  for (int r = 1; r < 16; ++r) mx = fmaxf(mx, fmaxf(sacc[0][r], sacc[1][r]));
-  maybe_raise<D>(w, pair_max(mx) * w.sl2);
-  const float m_use = (w.m_run == -INFINITY) ? 0.f : w.m_run;
-  bf16x8 pf0[2], pf1[2];
-  w.l_run += softmax_half<D>(w, sacc[0], m_use, pf0);
-  pv_half<D>(w, vs, pf0);
-  if (second) {
-    w.l_run += softmax_half<D>(w, sacc[1], m_use, pf1);
-    pv_half<D>(w, vs + 32 * ROWB, pf1);
+      for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          const int key = kb + 32 * h + 16 * b + 4 * w.quad + e;
+          if (key > w.limit[nb]) sc[h][b][nb][e] = -INFINITY;
+        }
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    if (h == 1 && !second) break;
+    bf16x8 pf[NB], v[Geo<D>::DB];
+    finish_half<D, NB>(w, sc[h], pf, softmax_half<D, NB>(w, sc[h], w.m_run, pf));
+    read_v<D, NB>(w, vs + h * 32 * ROWB, v);
+    pv_half<D, NB>(w, v, pf);
   }
 }
 
 // One 64-key tile read from buffer `ks`/`vs`; the DMA of the next tile goes to
 // `nk`/`nv`. The buffers are distinct LDS objects at each call site.
-template <int D>
-__device__ __forceinline__ void tile_step(WaveState<D> &w, const unsigned char *ks, const unsigned char *vs,
+template <int D, int NB>
+__device__ __forceinline__ void tile_step(WaveState<D, NB> &w, const unsigned char *ks, const unsigned char *vs,
                                           unsigned char *nk, unsigned char *nv, int kb, bool prefetch) {
   // Wait for this wave's DMA of this tile (the only vector-memory work in
   // flight; the compiler does not count LDS DMA as a store to release), then
@@ -339,13 +391,13 @@ __device__ __forceinline__ void tile_step(WaveState<D> &w, const unsigned char *
   __syncthreads();
   if (prefetch) dma_tile<Geo<D>::IPW>(w.kg, w.vg, kb + kBN, w.n_keys, w.kv_row_bytes, nk, nv, w.wave, w.dma_k, w.dma_v);
   if (kb > w.wave_last_key) return;               // the whole tile is masked for this wave
-  if (kb + kBN - 1 > w.wave_first_limit) tile_math<D, true>(w, ks, vs, kb);
-  else tile_math<D, false>(w, ks, vs, kb);
+  if (kb + kBN - 1 > w.wave_first_limit) tile_math<D, NB, true>(w, ks, vs, kb);
+  else tile_math<D, NB, false>(w, ks, vs, kb);
 }
 
 // One job: the work of launch slot `slot` of XCD `xcd` (one query head of one
 // work group, or one packed stage-2 unit group), run by the whole workgroup.
-template <int D, int KIND>
+template <int D, int KIND, int NB>
 __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, const int slot, unsigned char *k_lds0,
                                          unsigned char *v_lds0, unsigned char *k_lds1, unsigned char *v_lds1) {
   using Gm = Geo<D>;
@@ -403,40 +455,43 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
     }
   } else {
     h = g * G + hl;
-    wrow0 = mb * kAttnBM + wave * 32;
-    row_last = min(mb * kAttnBM + kAttnBM, n_rows) - 1;
+    wrow0 = (mb * 4 + wave) * (16 * NB);
+    row_last = min((mb + 1) * (64 * NB), n_rows) - 1;
   }
   const int k_begin = s * E.split_keys;
   const int k_end = min(min(k_begin + E.split_keys, n_keys), row_limit(E, row_last) + 1);
   const int n_tiles = k_end > k_begin ? (k_end - k_begin + kBN - 1) / kBN : 0;
 
   const int lane = tid & 63;
-  const int l32 = lane & 31;
-  const int half = lane >> 5;
-  const int my_row = wrow0 + l32;
+  const int l16 = lane & 15;
+  const int quad = lane >> 4;
+  const int my_row = wrow0 + l16;  // and my_row + 16 with NB = 2
   // keys above this are masked for the whole wave (a wave past the last row has none)
-  const int wave_last_key = wrow0 < n_rows ? row_limit(E, wrow0 + 31) : -1;
+  const int wave_last_key = wrow0 < n_rows ? row_limit(E, wrow0 + 16 * NB - 1) : -1;
 
-  WaveState<D> w;
+  WaveState<D, NB> w;
   w.kg = static_cast<const unsigned char *>(E.k);
   w.vg = static_cast<const unsigned char *>(E.v);
   w.n_keys = n_keys;
   w.kv_row_bytes = p.hkv * D * 2;
-  w.limit = row_limit(E, my_row);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) w.limit[nb] = row_limit(E, my_row + 16 * nb);
   w.wave_last_key = wave_last_key;
   w.wave_first_limit = row_limit(E, wrow0);
-  w.half = half;
+  w.quad = quad;
   w.wave = wave;
   w.sl2 = p.scale_log2;
-  w.m_run = -INFINITY;
-  w.l_run = 0.f;
 #pragma unroll
-  for (int db = 0; db < DB; ++db) w.oacc[db] = f32x16{};
-  {
-    const __bf16 *qp = static_cast<const __bf16 *>(E.q) + ((size_t)my_row * p.hq + h) * D + 8 * half;
+  for (int nb = 0; nb < NB; ++nb) {
+    w.m_run[nb] = kNoReference;
+    w.lacc[nb] = f32x4{};
+#pragma unroll
+    for (int db = 0; db < DB; ++db) w.oacc[nb][db] = f32x4{};
+    const int row = my_row + 16 * nb;
+    const __bf16 *qp = static_cast<const __bf16 *>(E.q) + ((size_t)row * p.hq + h) * D + 8 * quad;
 #pragma unroll
     for (int ds = 0; ds < DS; ++ds)
-      w.qf[ds] = my_row < n_rows ? *reinterpret_cast<const bf16x8 *>(qp + 16 * ds) : bf16x8{};
+      w.qf[nb][ds] = row < n_rows ? *reinterpret_cast<const bf16x8 *>(qp + 32 * ds) : bf16x8{};
   }
 #pragma unroll
   for (int i = 0; i < IPW; ++i) {
@@ -446,36 +501,35 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
     w.dma_v[i] = r * w.kv_row_bytes + g * D * 2 + ((pc ^ swz_v(r, CH)) << 4);
   }
 #pragma unroll
-  for (int ds = 0; ds < DS; ++ds) w.koff[ds] = l32 * ROWB + (((2 * ds + half) ^ swz_k(l32, CH)) << 4);
+  for (int ds = 0; ds < DS; ++ds) w.koff[ds] = l16 * ROWB + (((4 * ds + quad) ^ swz_k(l16, CH)) << 4);
   {
-    const int grp = lane >> 4, j = lane & 15;
+    // transposed read: lane 4 r + c of a 16-lane group addresses key 4 quad + r,
+    // features 4 c .. 4 c + 3 of the block, and receives 4 keys of one feature
+    const int key = 4 * quad + (l16 >> 2), sw = swz_v(key, CH);
 #pragma unroll
-    for (int b = 0; b < 2; ++b) {
-      const int key = 8 * b + 4 * (grp >> 1) + (j >> 2);
-      const int sw = swz_v(key, CH);
-#pragma unroll
-      for (int db = 0; db < DB; ++db) {
-        const int lc = 4 * db + 2 * (grp & 1) + ((j & 3) >> 1);
-        w.voff[db][b] = key * ROWB + ((lc ^ sw) << 4) + 8 * (j & 1);
-      }
-    }
+    for (int db = 0; db < DB; ++db)
+      w.voff[db] = key * ROWB + (((2 * db + ((l16 & 3) >> 1)) ^ sw) << 4) + 8 * (l16 & 1);
   }
 
   if (n_tiles > 0) dma_tile<IPW>(w.kg, w.vg, k_begin, n_keys, w.kv_row_bytes, k_lds0, v_lds0, wave, w.dma_k, w.dma_v);
   for (int t = 0; t < n_tiles; t += 2) {
     // even tiles live in buffer 0, odd tiles in buffer 1
     int kb = k_begin + t * kBN;
-    tile_step<D>(w, k_lds0, v_lds0, k_lds1, v_lds1, kb, t + 1 < n_tiles);
+    tile_step<D, NB>(w, k_lds0, v_lds0, k_lds1, v_lds1, kb, t + 1 < n_tiles);
     if (t + 1 < n_tiles) {
       kb += kBN;
-      tile_step<D>(w, k_lds1, v_lds1, k_lds0, v_lds0, kb, t + 2 < n_tiles);
+      tile_step<D, NB>(w, k_lds1, v_lds1, k_lds0, v_lds0, kb, t + 2 < n_tiles);
     }
   }
 
   // ---- epilogue ---------------------------------------------------------------
-  const float l_tot = pair_sum(w.l_run);
-  const float inv = l_tot > 0.f ? 1.f / l_tot : 0.f;
-  const float lse_nat = l_tot > 0.f ? (w.m_run + __log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
+  float inv[NB], lse_nat[NB];
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb) {
+    const float l_tot = w.lacc[nb][0];
+    inv[nb] = l_tot > 0.f ? 1.f / l_tot : 0.f;
+    lse_nat[nb] = l_tot > 0.f ? (w.m_run[nb] + __log2f(l_tot)) * 0.69314718055994531f : -INFINITY;
+  }
   // Rows go out through LDS so that every store is a 16-byte piece of a
   // contiguous row (a lane holds 4-feature pieces of one row, spread over the
   // row). Each wave stages in its own quarter of the stage buffer that did
@@ -483,42 +537,42 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
   // barrier and no copy targets it any more.
   unsigned char *stg = ((n_tiles & 1) ? (wave < 2 ? k_lds1 : v_lds1) : (wave < 2 ? k_lds0 : v_lds0)) +
                        (wave & 1) * (TILE / 2);
+#pragma unroll
+  for (int nb = 0; nb < NB; ++nb)
+#pragma unroll
+    for (int db = 0; db < DB; ++db) {
+      bf16x4 v;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) v[t] = (__bf16)(w.oacc[nb][db][t] * inv[nb]);
+      stage_put<D>(stg, nb * 16 + l16, 2 * db + (quad >> 1), 8 * (quad & 1), v);
+    }
   const int wrow = wrow0;  // first row of this wave
   if (E.n_splits == 1 && E.o != nullptr) {
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (__bf16)(w.oacc[db][4 * q4 + t] * inv);
-        stage_put<D>(stg, l32, 4 * db + q4, 8 * half, v);
-      }
-    store_rows<D>(stg, lane, wrow, n_rows, [&](int r) {
+    store_rows<D, 16 * NB>(stg, lane, wrow, n_rows, [&](int r) {
       return static_cast<unsigned char *>(E.o) + ((size_t)r * p.hq + h) * D * 2;
     });
     if (E.o2 != nullptr)
-      store_rows<D>(stg, lane, wrow, n_rows, [&](int r) {
+      store_rows<D, 16 * NB>(stg, lane, wrow, n_rows, [&](int r) {
         const int64_t r2 = E.o2_row0 + (E.o2_idx ? E.o2_idx[r] : r);
         return static_cast<unsigned char *>(E.o2) + ((size_t)r2 * p.hq + h) * D * 2;
       });
-    if (E.lse != nullptr && half == 0 && my_row < n_rows) E.lse[(size_t)h * E.lse_stride + my_row] = lse_nat;
+    if (E.lse != nullptr && quad == 0) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        if (my_row + 16 * nb < n_rows) E.lse[(size_t)h * E.lse_stride + my_row + 16 * nb] = lse_nat[nb];
+    }
   } else {
     // bf16 partials (the normalised split output, like a final output row)
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        bf16x4 v;
-#pragma unroll
-        for (int t = 0; t < 4; ++t) v[t] = (__bf16)(w.oacc[db][4 * q4 + t] * inv);
-        stage_put<D>(stg, l32, 4 * db + q4, 8 * half, v);
-      }
-    store_rows<D>(stg, lane, wrow, n_rows, [&](int r) {
+    store_rows<D, 16 * NB>(stg, lane, wrow, n_rows, [&](int r) {
       const size_t prow = (size_t)r * E.n_splits + s;
       return static_cast<unsigned char *>(E.part_o) + (prow * p.hq + h) * D * 2;
     });
-    if (half == 0 && my_row < n_rows) E.part_lse[((size_t)my_row * E.n_splits + s) * p.hq + h] = lse_nat;
+    if (quad == 0) {
+#pragma unroll
+      for (int nb = 0; nb < NB; ++nb)
+        if (my_row + 16 * nb < n_rows)
+          E.part_lse[((size_t)(my_row + 16 * nb) * E.n_splits + s) * p.hq + h] = lse_nat[nb];
+    }
   }
 }
 
@@ -527,7 +581,7 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
 // with a light one, so that their sums are nearly equal), and every further
 // workgroup runs one of the remaining, lightest slots. With pair_wgs = 0 each
 // workgroup runs one slot.
-template <int D, int KIND>
+template <int D, int KIND, int NB>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_bf16_kernel(const AttnLaunch p) {
   constexpr int TILE = Geo<D>::TILE;
   // separate objects per stage and tensor: lets the compiler see that the DMA
@@ -544,13 +598,32 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_bf16_kernel(const AttnLa
   const int n_jobs = (paired && second < p.slots_per_xcd) ? 2 : 1;
   for (int j = 0; j < n_jobs; ++j) {
     if (j) __syncthreads();  // every wave is done with the LDS buffers of the first job
-    attn_job<D, KIND>(p, xcd, j ? second : first, k_lds0, v_lds0, k_lds1, v_lds1);
+    attn_job<D, KIND, NB>(p, xcd, j ? second : first, k_lds0, v_lds0, k_lds1, v_lds1);
   }
 }
 
 template <int D>
 hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
   AttnLaunch p = p0;
+  // Causal self attention of at most kNarrowJobs 128-row blocks (times heads)
+  // runs 64-row blocks, 16 rows per wave: twice the workgroups, and the longest
+  // block's chain of key tiles, which is what such a launch takes, is shorter
+  // per tile. n = 512 / 922 / 1500 of 28 heads (112 / 224 / 336 blocks): 14.6 /
+  // 21.6 / 33.5 us with 128 rows, 10.7 / 17.0 / 27.3 with 64; n = 2000 (448)
+  // 43.2 and 42.7, n = 2458 (560) 54.7 and 57.4: above, the slots are full and
+  // the doubled K/V copies per row cost more.
+  constexpr int kNarrowJobs = 448;
+  const bool narrow = kind == AttnKind::kSelf && p.n_groups * p.group <= kNarrowJobs;
+  if (narrow) {
+    p.n_groups = 0;
+    for (int i = 0; i < p.n_entries; ++i) {
+      AttnEntry &e = p.e[i];
+      e.mb_count = (e.n_rows + 63) / 64;
+      e.mb_hi = e.mb_count - 1;
+      e.group0 = p.n_groups;
+      p.n_groups += e.mb_count * p.hkv;
+    }
+  }
   // slots per XCD: work groups per XCD times the G heads of a work group
   int per_xcd;
   if (kXcds % p.hkv == 0) {
@@ -574,8 +647,11 @@ hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
   const int wgs = p.pair_wgs ? p.pair_wgs + std::max(0, slots - 2 * p.pair_wgs) : slots;
   const dim3 grid(kXcds * wgs), block(kAttnThreads);
   switch (kind) {
-    case AttnKind::kSelf: attn_bf16_kernel<D, 0><<<grid, block, 0, st>>>(p); break;
-    default: attn_bf16_kernel<D, 1><<<grid, block, 0, st>>>(p); break;
+    case AttnKind::kSelf:
+      if (narrow) attn_bf16_kernel<D, 0, 1><<<grid, block, 0, st>>>(p);
+      else attn_bf16_kernel<D, 0, 2><<<grid, block, 0, st>>>(p);
+      break;
+    default: attn_bf16_kernel<D, 1, 2><<<grid, block, 0, st>>>(p); break;
   }
   return hipGetLastError();
 }
