@@ -161,10 +161,25 @@ def _ptr(x):
     return x.data_ptr() or None
 
 
+_raw_stream = None
+
+
+def _current_stream():
+    """torch's current stream (an address), or None without a GPU."""
+    global _raw_stream
+    if _raw_stream is None:
+        import torch
+        if not torch.cuda.is_available():
+            return None
+        torch.cuda.init()
+        device, raw = torch.cuda.current_device, torch._C._cuda_getCurrentRawStream
+        _raw_stream = lambda: raw(device()) or None  # noqa: E731
+    return _raw_stream()
+
+
 def _stream(stream):
     if stream is None:
-        import torch
-        return torch.cuda.current_stream().cuda_stream if torch.cuda.is_available() else None
+        return _current_stream()
     if isinstance(stream, int):
         return stream or None
     return stream.cuda_stream

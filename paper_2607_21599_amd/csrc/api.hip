@@ -164,7 +164,15 @@ std::vector<Split> plan_splits(const Cfg &c, const Batch &b) {
     const int wgs = packed_qdoc(c) ? c.hkv * qdoc_blocks(c, q.L_q) : c.hq * qdoc_blocks(c, q.L_q);
     work += (double)wgs * kbs;
   }
-  const double per_wg = std::max(1.0, work / kTargetWorkgroups);
+  // key tiles per workgroup for two workgroups per CU; where that is few, one
+  // per CU: a workgroup's fixed cost (about 5 us), its partial rows and the
+  // merge then weigh more than the longer chain (3 tiles, 6k keys and 64 rows:
+  // the call 21.1 us with two per CU, 19.2 with one; 8 tiles, 32k keys and 32
+  // rows: 30.1 and 30.0; 14 tiles, 16k keys and 128 rows: 4-8 us slower with one).
+  // The fp32 kernel's tiles take several times as long, so it keeps two.
+  double per_wg = work / kTargetWorkgroups;
+  if (packed_qdoc(c) && per_wg < 5.0) per_wg *= 2.0;
+  per_wg = std::max(1.0, per_wg);
   std::vector<Split> out(b.r.size());
   for (size_t i = 0; i < b.r.size(); ++i) {
     const Req &q = b.r[i];
@@ -199,7 +207,7 @@ WsLayout ws_layout(const Cfg &c, const Batch &b, const std::vector<Split> &sp) {
 }
 
 // ---- second stream for the layer call ----------------------------------------
-// daf_layer_attn runs stage 1 on a library-owned stream (default priority),
+// daf_layer_attn runs a large stage 1 on a library-owned stream (default priority),
 // forked from and joined back into the caller's stream by events, so that it
 // overlaps the KV write-back, stage 2 and the merge. One stream and two events
 // per device, created on first use; the mutex keeps each call's fork and join
@@ -311,27 +319,62 @@ AttnEntry qdoc_entry(const Cfg &c, const Req &q, const Split &sp, int64_t part_r
 
 int entry_groups(const Cfg &c, const AttnEntry &e) { return e.mb_count * e.n_splits * c.hkv; }
 
-daf_status_t run_entries(const Cfg &c, AttnKind kind, std::vector<AttnEntry> &entries, hipStream_t st) {
+AttnLaunch new_launch(const Cfg &c) {
+  AttnLaunch p{};
+  p.hq = c.hq;
+  p.hkv = c.hkv;
+  p.group = c.group;
+  p.scale_log2 = c.scale * 1.4426950408889634f;
+  return p;
+}
+
+// Append entries i0 .. i1 to list l of the launch.
+void add_list(const Cfg &c, AttnLaunch &p, AttnList &l, AttnKind kind, const std::vector<AttnEntry> &entries,
+              size_t i0, size_t i1) {
+  l.wgs_per_group = (kind == AttnKind::kQdoc && packed_qdoc(c)) ? 1 : c.group;
+  for (size_t i = i0; i < i1; ++i) {
+    AttnEntry &e = p.e[l.e0 + l.n_entries++];
+    e = entries[i];
+    e.group0 = l.n_groups;
+    l.n_groups += entry_groups(c, e);
+  }
+}
+
+daf_status_t run_entries(const Cfg &c, AttnKind kind, const std::vector<AttnEntry> &entries, hipStream_t st) {
   for (size_t i0 = 0; i0 < entries.size(); i0 += kMaxEntries) {
-    AttnLaunch p{};
-    p.hq = c.hq;
-    p.hkv = c.hkv;
-    p.group = c.group;
-    p.wgs_per_group = (kind == AttnKind::kQdoc && packed_qdoc(c)) ? 1 : c.group;
-    p.scale_log2 = c.scale * 1.4426950408889634f;
-    int groups = 0;
-    const size_t i1 = std::min(entries.size(), i0 + kMaxEntries);
-    for (size_t i = i0; i < i1; ++i) {
-      AttnEntry e = entries[i];
-      e.group0 = groups;
-      groups += entry_groups(c, e);
-      p.e[p.n_entries++] = e;
-    }
-    p.n_groups = groups;
+    AttnLaunch p = new_launch(c);
+    add_list(c, p, p.list[0], kind, entries, i0, std::min(entries.size(), i0 + kMaxEntries));
     hipError_t err = launch_attention(c.dtype, c.d, kind, p, st);
     if (err != hipSuccess) return hip_fail(err, "attention launch");
   }
   return DAF_OK;
+}
+
+// Whether the layer call runs both stages in one launch: stage 1 is small
+// (kNarrowJobs) and the work tables fit one launch. Such a layer is bound by
+// launches and by the longest chain of key tiles, which the other stage's
+// workgroups then run beside; the second stream's two events and waits cost
+// about 20 us of host time. Layers above the line fill the chip with each
+// stage, and one launch for both was slower than two (287-304 against 277 us at
+// 32k).
+bool one_launch(const Cfg &c, const std::vector<AttnEntry> &self, const std::vector<AttnEntry> &qdoc) {
+  if (self.empty() || qdoc.empty() || self.size() + qdoc.size() > (size_t)kMaxEntries) return false;
+  int64_t jobs = 0;
+  for (const AttnEntry &e : self) jobs += (int64_t)e.mb_count * c.hq;
+  return jobs <= kNarrowJobs;
+}
+
+daf_status_t run_both(const Cfg &c, const std::vector<AttnEntry> &self, const std::vector<AttnEntry> &qdoc,
+                      hipStream_t st) {
+  AttnLaunch p = new_launch(c);
+  add_list(c, p, p.list[0], AttnKind::kSelf, self, 0, self.size());
+  // the fp32 kernel takes split and direct entries in one list
+  AttnList &l2 = p.list[c.dtype == DAF_BF16 ? 1 : 0];
+  if (c.dtype == DAF_BF16) l2.e0 = p.list[0].n_entries;
+  add_list(c, p, l2, AttnKind::kQdoc, qdoc, 0, qdoc.size());
+  const hipError_t err = c.dtype == DAF_BF16 ? launch_attention_both_bf16(c.d, p, st)
+                                             : launch_attention(c.dtype, c.d, AttnKind::kSelf, p, st);
+  return err == hipSuccess ? DAF_OK : hip_fail(err, "attention launch");
 }
 
 void add_self_entries(const Cfg &c, const Batch &b, const void *q_imp, const void *k_imp,
@@ -521,6 +564,13 @@ daf_status_t layer_attn_impl(const Cfg &c, const Batch &b, const int32_t *idx, c
   // important rows of hidden; the hybrid KV (which stage 2 reads), stage 2
   // and the merge (question rows of hidden) touch none of that, so stage 1
   // runs beside them on the second stream.
+  if (one_launch(c, self, qdoc.attn)) {
+    CHECK(fuse_impl(c, b, DAF_FUSE_KV, idx, k_imp, v_imp, k_q, v_q, k_cache, v_cache, nullptr, nullptr, nullptr,
+                    stream));
+    CHECK(run_both(c, self, qdoc.attn, stream));
+    CHECK(run_merge(c, qdoc.merge, stream));
+    return ok();
+  }
   std::lock_guard<std::mutex> lock(g_aux_mu);
   AuxStream *ax = (self.empty() || !fork) ? nullptr : aux_stream();
   daf_status_t st1 = DAF_OK;

@@ -101,9 +101,9 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_fwd_kernel(const AttnLau
   const int slot = blockIdx.x / kXcds;
   const int gamma = (slot / G) * kXcds + xcd;
   const int hl = slot % G;
-  if (gamma >= p.n_groups) return;
+  if (gamma >= p.list[0].n_groups) return;
   int ei = 0;
-  while (ei + 1 < p.n_entries && p.e[ei + 1].group0 <= gamma) ++ei;
+  while (ei + 1 < p.list[0].n_entries && p.e[ei + 1].group0 <= gamma) ++ei;
   const AttnEntry &E = p.e[ei];
   int gl = gamma - E.group0;
   const int g = gl % p.hkv;
@@ -408,7 +408,7 @@ __global__ __launch_bounds__(256) void lse_merge_kernel(const MergeLaunch p) {
 
 template <typename T, int D>
 hipError_t launch_attn_t(AttnKind kind, const AttnLaunch &p, hipStream_t st) {
-  const int slots = p.wgs_per_group * ((p.n_groups + kXcds - 1) / kXcds);
+  const int slots = p.list[0].wgs_per_group * ((p.list[0].n_groups + kXcds - 1) / kXcds);
   const dim3 grid(kXcds * slots), block(kAttnThreads);
   switch (kind) {
     case AttnKind::kSelf: attn_fwd_kernel<T, D, 0><<<grid, block, 0, st>>>(p); break;
@@ -429,7 +429,7 @@ hipError_t launch_merge_t(const MergeLaunch &p, hipStream_t st) {
 
 hipError_t launch_attention(int dtype, int head_dim, AttnKind kind, const AttnLaunch &p,
                             hipStream_t st) {
-  if (p.n_groups <= 0) return hipSuccess;
+  if (p.list[0].n_groups <= 0) return hipSuccess;
   if (dtype == 0) return launch_attention_bf16(head_dim, kind, p, st);
   return head_dim == 128 ? launch_attn_t<float, 128>(kind, p, st)
                          : launch_attn_t<float, 64>(kind, p, st);

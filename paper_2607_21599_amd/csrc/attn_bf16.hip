@@ -398,7 +398,7 @@ __device__ __forceinline__ void tile_step(WaveState<D, NB> &w, const unsigned ch
 // One job: the work of launch slot `slot` of XCD `xcd` (one query head of one
 // work group, or one packed stage-2 unit group), run by the whole workgroup.
 template <int D, int KIND, int NB>
-__device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, const int slot, unsigned char *k_lds0,
+__device__ __forceinline__ void attn_job(const AttnLaunch &p, const AttnList &l, const int xcd, const int slot, unsigned char *k_lds0,
                                          unsigned char *v_lds0, unsigned char *k_lds1, unsigned char *v_lds1) {
   using Gm = Geo<D>;
   constexpr int ROWB = Gm::ROWB, CH = Gm::CH, TILE = Gm::TILE, IPW = Gm::IPW, DS = Gm::DS, DB = Gm::DB;
@@ -411,7 +411,7 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
   // otherwise work groups are dealt to the XCDs round-robin. Within an XCD,
   // work groups run heaviest first, and the G heads of a work group are
   // consecutive workgroups of that XCD.
-  const int G = p.group, WPG = p.wgs_per_group;
+  const int G = p.group, WPG = l.wgs_per_group;
   const int hl = slot % WPG;
   int g, lam;  // KV head, index of the work group among that head's work groups
   if (kXcds % p.hkv == 0) {
@@ -421,15 +421,15 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const int xcd, con
     // (a, b, b, a, ...), so the XCDs get equal shares of the heaviest-first list
     const int q = slot / WPG, r = xcd % xph;
     lam = q * xph + ((q & 1) ? xph - 1 - r : r);
-    if (lam * p.hkv >= p.n_groups) return;
+    if (lam * p.hkv >= l.n_groups) return;
   } else {
     const int gamma = (slot / WPG) * kXcds + xcd;
-    if (gamma >= p.n_groups) return;
+    if (gamma >= l.n_groups) return;
     g = gamma % p.hkv;
     lam = gamma / p.hkv;
   }
-  int ei = 0;
-  while (ei + 1 < p.n_entries && p.e[ei + 1].group0 <= lam * p.hkv) ++ei;
+  int ei = l.e0;
+  while (ei + 1 < l.e0 + l.n_entries && p.e[ei + 1].group0 <= lam * p.hkv) ++ei;
   const AttnEntry &E = p.e[ei];
   const int ll = lam - E.group0 / p.hkv;
   const int s = ll % E.n_splits;
@@ -592,19 +592,62 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_bf16_kernel(const AttnLa
   __shared__ __attribute__((aligned(1024))) unsigned char v_lds1[TILE];
   const int xcd = blockIdx.x % kXcds;
   const int u = blockIdx.x / kXcds;
-  const bool paired = u < p.pair_wgs;
-  const int first = paired ? u : u + p.pair_wgs;
-  const int second = 2 * p.pair_wgs - 1 - u;
-  const int n_jobs = (paired && second < p.slots_per_xcd) ? 2 : 1;
+  const AttnList &l = p.list[0];
+  const bool paired = u < l.pair_wgs;
+  const int first = paired ? u : u + l.pair_wgs;
+  const int second = 2 * l.pair_wgs - 1 - u;
+  const int n_jobs = (paired && second < l.slots_per_xcd) ? 2 : 1;
   for (int j = 0; j < n_jobs; ++j) {
     if (j) __syncthreads();  // every wave is done with the LDS buffers of the first job
-    attn_job<D, KIND, NB>(p, xcd, j ? second : first, k_lds0, v_lds0, k_lds1, v_lds1);
+    attn_job<D, KIND, NB>(p, l, xcd, j ? second : first, k_lds0, v_lds0, k_lds1, v_lds1);
+  }
+}
+
+// Both stages in one launch, for small layers (64-row blocks in stage 1, the
+// longest chains of key tiles first). QDOC_FIRST: the first workgroups of each
+// XCD run stage 2 and the rest stage 1, else the other way round.
+template <int D, bool QDOC_FIRST>
+__global__ __launch_bounds__(kAttnThreads, 2) void attn_both_kernel(const AttnLaunch p) {
+  constexpr int TILE = Geo<D>::TILE;
+  __shared__ __attribute__((aligned(1024))) unsigned char k_lds0[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_lds0[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char k_lds1[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_lds1[TILE];
+  const int xcd = blockIdx.x % kXcds, u = blockIdx.x / kXcds;
+  const int n1 = QDOC_FIRST ? 0 : p.list[0].slots_per_xcd, n2 = QDOC_FIRST ? p.list[1].slots_per_xcd : 0;
+  const bool self = QDOC_FIRST ? u >= n2 : u < n1;
+  if (self) attn_job<D, 0, 1>(p, p.list[0], xcd, u - n2, k_lds0, v_lds0, k_lds1, v_lds1);
+  else attn_job<D, 1, 2>(p, p.list[1], xcd, u - n1, k_lds0, v_lds0, k_lds1, v_lds1);
+}
+
+// Slots per XCD of a list: work groups per XCD times the workgroups of one.
+int list_slots(const AttnLaunch &p, const AttnList &l) {
+  int per_xcd;
+  if (kXcds % p.hkv == 0) {
+    const int xph = kXcds / p.hkv, per_head = l.n_groups / p.hkv;
+    per_xcd = (per_head + xph - 1) / xph;
+  } else {
+    per_xcd = (l.n_groups + kXcds - 1) / kXcds;
+  }
+  return l.wgs_per_group * per_xcd;
+}
+
+// The entries of a self-attention list in 64-row blocks.
+void narrow_blocks(AttnLaunch &p, AttnList &l) {
+  l.n_groups = 0;
+  for (int i = l.e0; i < l.e0 + l.n_entries; ++i) {
+    AttnEntry &e = p.e[i];
+    e.mb_count = (e.n_rows + 63) / 64;
+    e.mb_hi = e.mb_count - 1;
+    e.group0 = l.n_groups;
+    l.n_groups += e.mb_count * p.hkv;
   }
 }
 
 template <int D>
 hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
   AttnLaunch p = p0;
+  AttnList &l = p.list[0];
   // Causal self attention of at most kNarrowJobs 128-row blocks (times heads)
   // runs 64-row blocks, 16 rows per wave: twice the workgroups, and the longest
   // block's chain of key tiles, which is what such a launch takes, is shorter
@@ -612,39 +655,21 @@ hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
   // 21.6 / 33.5 us with 128 rows, 10.7 / 17.0 / 27.3 with 64; n = 2000 (448)
   // 43.2 and 42.7, n = 2458 (560) 54.7 and 57.4: above, the slots are full and
   // the doubled K/V copies per row cost more.
-  constexpr int kNarrowJobs = 448;
-  const bool narrow = kind == AttnKind::kSelf && p.n_groups * p.group <= kNarrowJobs;
-  if (narrow) {
-    p.n_groups = 0;
-    for (int i = 0; i < p.n_entries; ++i) {
-      AttnEntry &e = p.e[i];
-      e.mb_count = (e.n_rows + 63) / 64;
-      e.mb_hi = e.mb_count - 1;
-      e.group0 = p.n_groups;
-      p.n_groups += e.mb_count * p.hkv;
-    }
-  }
-  // slots per XCD: work groups per XCD times the G heads of a work group
-  int per_xcd;
-  if (kXcds % p.hkv == 0) {
-    const int xph = kXcds / p.hkv, per_head = p.n_groups / p.hkv;
-    per_xcd = (per_head + xph - 1) / xph;
-  } else {
-    per_xcd = (p.n_groups + kXcds - 1) / kXcds;
-  }
-  const int slots = p.wgs_per_group * per_xcd;
+  const bool narrow = kind == AttnKind::kSelf && l.n_groups * p.group <= kNarrowJobs;
+  if (narrow) narrow_blocks(p, l);
+  const int slots = list_slots(p, l);
   // Causal self attention: the heaviest 2 * kResidentPerXcd slots of an XCD
   // run in heavy/light pairs (see the kernel). Slots are in heaviest-first
   // order within an entry, and entries heaviest request first, so the pairing
   // is used when the first entry alone fills those slots.
   const int xph = kXcds % p.hkv == 0 ? kXcds / p.hkv : 0;
   const int first_groups = xph ? p.e[0].mb_count / xph : p.e[0].mb_count * p.hkv / kXcds;
-  p.slots_per_xcd = slots;
-  p.pair_wgs = (kind == AttnKind::kSelf && p.e[0].n_splits == 1 &&
-                first_groups * p.wgs_per_group >= 2 * kResidentPerXcd)
+  l.slots_per_xcd = slots;
+  l.pair_wgs = (kind == AttnKind::kSelf && p.e[0].n_splits == 1 &&
+                first_groups * l.wgs_per_group >= 2 * kResidentPerXcd)
                    ? kResidentPerXcd
                    : 0;
-  const int wgs = p.pair_wgs ? p.pair_wgs + std::max(0, slots - 2 * p.pair_wgs) : slots;
+  const int wgs = l.pair_wgs ? l.pair_wgs + std::max(0, slots - 2 * l.pair_wgs) : slots;
   const dim3 grid(kXcds * wgs), block(kAttnThreads);
   switch (kind) {
     case AttnKind::kSelf:
@@ -653,6 +678,26 @@ hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
       break;
     default: attn_bf16_kernel<D, 1, 2><<<grid, block, 0, st>>>(p); break;
   }
+  return hipGetLastError();
+}
+
+template <int D>
+hipError_t launch_both_t(const AttnLaunch &p0, hipStream_t st) {
+  AttnLaunch p = p0;
+  narrow_blocks(p, p.list[0]);
+  for (AttnList &l : p.list) l.slots_per_xcd = list_slots(p, l);
+  // The stage with the longer jobs first. A stage-2 tile (32 rows a wave, every
+  // slot taken) costs more than a stage-1 tile, whose shorter blocks also fill
+  // in behind: stage 2 first from a quarter of stage 1's longest chain. Layer,
+  // stage 1 / stage 2 first: 16k keys, n = 819, 128 rows (13 and 14 tiles) 62.3
+  // / 57.1 us; 32k, n = 1638, 16 rows (26 and 8) 67.1 / 62.9; 6k, n = 922, 64
+  // rows (15 and 3) 38.7 / 39.4.
+  int chain1 = 0, chain2 = 0;
+  for (int i = 0; i < p.list[0].n_entries; ++i) chain1 = std::max(chain1, (p.e[i].n_keys + kBN - 1) / kBN);
+  for (int i = 0; i < p.list[1].n_entries; ++i) chain2 = std::max(chain2, p.e[p.list[1].e0 + i].split_keys / kBN);
+  const dim3 grid(kXcds * (p.list[0].slots_per_xcd + p.list[1].slots_per_xcd)), block(kAttnThreads);
+  if (4 * chain2 > chain1) attn_both_kernel<D, true><<<grid, block, 0, st>>>(p);
+  else attn_both_kernel<D, false><<<grid, block, 0, st>>>(p);
   return hipGetLastError();
 }
 
@@ -744,8 +789,12 @@ hipError_t launch_qdoc_merge_t(const MergeLaunch &p, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_attention_bf16(int head_dim, AttnKind kind, const AttnLaunch &p, hipStream_t st) {
-  if (p.n_groups <= 0) return hipSuccess;
+  if (p.list[0].n_groups <= 0) return hipSuccess;
   return head_dim == 128 ? launch_t<128>(kind, p, st) : launch_t<64>(kind, p, st);
+}
+
+hipError_t launch_attention_both_bf16(int head_dim, const AttnLaunch &p, hipStream_t st) {
+  return head_dim == 128 ? launch_both_t<128>(p, st) : launch_both_t<64>(p, st);
 }
 
 hipError_t launch_qdoc_merge_bf16(int head_dim, const MergeLaunch &p, hipStream_t st) {

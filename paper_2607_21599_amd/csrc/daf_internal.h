@@ -55,24 +55,27 @@ __device__ __forceinline__ int row_limit(const AttnEntry &e, int r) {
   return e.q_pos ? e.q_pos[rr] : rr + (e.n_keys - e.n_rows);
 }
 
-struct AttnLaunch;
-static_assert(sizeof(AttnEntry) * kMaxEntries + 64 < 4096, "attention launch table must fit 4 KiB of kernel arguments");
-struct AttnLaunch {
-  int32_t hq, hkv, group;  // group = Hq / Hkv
+// Work list of one stage in an attention launch: entries e0 .. e0 + n_entries.
+struct AttnList {
   // workgroups per work group: G (one query head each, 128 rows) or, for the
   // bf16 split-key kernel, 1 (packed: the workgroup's 4 waves take 4
   // consecutive (head, 32-row block) units of the KV group, so every K/V tile
   // it copies serves several heads when the question is short)
   int32_t wgs_per_group;
-  int32_t n_entries;
-  int32_t n_groups;        // total work groups over all entries
-  float scale_log2;        // softmax scale * log2(e)
+  int32_t e0, n_entries;
+  int32_t n_groups;        // total work groups over the entries
   // launch shape, set by the launcher: slots per XCD, and the number of
   // workgroups per XCD that run two slots (a heavy and a light one; 0 = none)
   int32_t slots_per_xcd;
   int32_t pair_wgs;
+};
+struct AttnLaunch {
+  int32_t hq, hkv, group;  // group = Hq / Hkv
+  float scale_log2;        // softmax scale * log2(e)
+  AttnList list[2];        // list[1]: stage 2 beside stage 1 in one launch (bf16), else unused
   AttnEntry e[kMaxEntries];
 };
+static_assert(sizeof(AttnLaunch) < 4096, "attention launch table must fit 4 KiB of kernel arguments");
 
 // Log-sum-exp merge of split partials, one request per entry.
 struct MergeEntry {
@@ -150,6 +153,11 @@ hipError_t launch_attention(int dtype, int head_dim, AttnKind kind,
                             const AttnLaunch &p, hipStream_t s);
 hipError_t launch_attention_bf16(int head_dim, AttnKind kind, const AttnLaunch &p,
                                  hipStream_t s);
+// Stage 1 (list[0], at most kNarrowJobs blocks) and stage 2 (list[1]) in one launch (bf16).
+hipError_t launch_attention_both_bf16(int head_dim, const AttnLaunch &p, hipStream_t s);
+// Causal self attention of at most this many 128-row blocks times heads runs
+// 64-row blocks (attn_bf16.hip), and the layer call runs both stages in one launch.
+constexpr int kNarrowJobs = 448;
 hipError_t launch_merge(int dtype, int head_dim, const MergeLaunch &p,
                         hipStream_t s);
 // merge of the bf16 stage-2 split partials (attn_bf16.hip)

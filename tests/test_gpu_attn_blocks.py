@@ -57,3 +57,38 @@ def test_stage1_block_height_ragged():
 @pytest.mark.parametrize("n", [700, 2200])
 def test_stage1_reference_raised_late(n):
     _run([di.Shape("loud", L_d=n + 5, L_q=1, n=n, seed=9)], loud=(70, n // 3, n // 2 + 1))
+
+
+@pytest.mark.parametrize("reqs,hq,hkv,d,dtype", [
+    ([(4000, 128, 300)], 28, 4, 128, di.BF16),   # one launch, stage 2 first (its jobs are the longer ones)
+    ([(3000, 8, 900)], 28, 4, 128, di.BF16),     # one launch, stage 1 first
+    ([(2500, 40, 1200), (300, 9, 5), (64, 70, 0), (700, 0, 100)], 8, 2, 64, di.BF16),
+    ([(900, 33, 200), (500, 5, 130)], 4, 1, 64, di.F32),
+    ([(700, 20, 90)], 14, 2, 128, di.F32),
+    ([(200 + 10 * i, 3 + i, 20 + i) for i in range(20)], 7, 1, 128, di.BF16),  # 40 entries: two launches
+    ([(2100, 16, 2048)], 28, 4, 128, di.BF16), ([(2100, 16, 2049)], 28, 4, 128, di.BF16)])  # the rule's line
+def test_layer_equals_stage_calls(reqs, hq, hkv, d, dtype):
+    """The layer call in either launch form writes what the stage calls write,
+    bit for bit, and the stage calls' outputs are the oracle's."""
+    from paper_2607_21599_amd.tensors import LayerBuffers
+    shapes = [di.Shape(f"l{i}", L_d=r[0], L_q=r[1], n=r[2], hq=hq, hkv=hkv, d=d, dtype=dtype, seed=700 + i)
+              for i, r in enumerate(reqs)]
+    batch = di.make_batch(shapes)
+    a, b = (LayerBuffers(batch.arrays, batch.cu_doc, batch.cu_q, batch.cu_imp, hq, hkv, d) for _ in range(2))
+    a["ws"].fill_(0xff)  # the workspace starts as NaNs
+    a.layer()
+    b.fuse_kv()
+    b.stage1()
+    b.stage2()
+    b.fuse_hidden()
+    torch.cuda.synchronize()
+    for k in ("o_imp", "o_q", "lse_imp", "lse_q", "hidden", "k_cache", "v_cache"):
+        assert torch.equal(a[k].view(torch.uint8), b[k].view(torch.uint8)), k
+    for i, s in enumerate(shapes[:4]):
+        rows = sample_rows(s.n, 24, seed=s.n)
+        ref = oracle_request(batch.request(i), rows1=rows)
+        if s.n:
+            assert_attn_close(b["o_imp"].float().cpu().numpy()[int(batch.cu_imp[i]) + rows], ref["o_imp"], dtype, "stage 1")
+        if s.L_q:
+            q = slice(int(batch.cu_q[i]), int(batch.cu_q[i + 1]))
+            assert_attn_close(b["o_q"].float().cpu().numpy()[q], ref["o_q"], dtype, "stage 2")
