@@ -48,13 +48,16 @@ namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 typedef __attribute__((address_space(3))) unsigned char lds_u8;
 
 constexpr int kTK = 64;          // k step
 constexpr int kRegion = 16384;   // LDS region: 128 rows x 128 bytes
 constexpr int kGroupM = 8;       // M-tiles per group of the tile order
 constexpr int kCus = 256;
-[[maybe_unused]] constexpr int kRsrcWord3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
+constexpr int kSlots = 10;       // regions in LDS (all 160 KiB)
+constexpr int kLds = kSlots * kRegion;
+[[maybe_unused]] constexpr unsigned kRsrcWord3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 
 struct GemmPlan {
   GemmJob j;
@@ -80,18 +83,37 @@ __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Copy a region: this wave writes rows 16 wave .. 16 wave + 15 (two 1 KiB
-// instructions); bytes at or past `nrec` from `base` read as zero.
-__device__ __forceinline__ void copy_region(const unsigned char *base, uint32_t nrec, unsigned char *lds, int wave,
+// Copy a region into LDS at byte `lds`: this wave writes rows 16 wave .. 16
+// wave + 15 (two 1 KiB instructions); bytes at or past `nrec` from `base` read
+// as zero. In asm, so that the compiler does not wait for the copies in flight
+// at each LDS read: wait_vm counts them, the phase barriers order them.
+__device__ __forceinline__ void copy_region(const unsigned char *base, uint32_t nrec, uint32_t lds,
                                             const uint32_t (&voff)[2]) {
 #if defined(__HIP_DEVICE_COMPILE__)
-  const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, nrec, kRsrcWord3);
-#pragma unroll
-  for (int i = 0; i < 2; ++i)
-    __builtin_amdgcn_raw_ptr_buffer_load_lds(
-        r, (void __attribute__((address_space(3))) *)((lds_u8 *)lds + (wave * 2 + i) * 1024), 16, (int)voff[i], 0, 0,
-        0);
+  const uint64_t a = (uint64_t)base;
+  u32x4 r;
+  r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
+  r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
+  r[2] = __builtin_amdgcn_readfirstlane(nrec);
+  r[3] = kRsrcWord3;
+  asm volatile(
+      "s_mov_b32 m0, %0\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %2, %4, 0 offen lds\n\t"
+      "s_mov_b32 m0, %1\n\t"
+      "s_nop 0\n\t"
+      "buffer_load_dwordx4 %3, %4, 0 offen lds"
+      :
+      : "s"(lds), "s"(lds + 1024), "v"(voff[0]), "v"(voff[1]), "s"(r)
+      : "memory");
 #endif
+}
+
+// LDS byte of the slot n after `at`.
+template <int N>
+__device__ __forceinline__ uint32_t slot_after(uint32_t at) {
+  const uint32_t x = at + N * kRegion;
+  return x >= (uint32_t)kLds ? x - kLds : x;
 }
 
 // Per-wave state of a tile of H 128-row halves.
@@ -99,43 +121,55 @@ template <int H>
 struct Tile {
   f32x4 acc[H][2][4][2];  // [row half][column half][16 rows][16 columns], D^T blocks: a lane holds 4 columns of a row
   bf16x8 a[4][2];         // fragments of one row half: [16 rows][32 k]
-  bf16x8 b0[2][2][2], b1[2][2];  // column halves 0 (two sets) and 1: [16 columns][32 k]
+  bf16x8 b[2][2][2];      // fragments of the column halves: [half][16 columns][32 k]
   int fa[2], fb[2];       // LDS read offsets per 32 k
   uint32_t va[2], vb[2];  // copy source offsets
   const unsigned char *A, *W0, *W1;  // tile origin; the two column halves' weight rows
   uint32_t na, nb0, nb1;  // valid bytes from A, W0, W1
   uint32_t a_half;        // bytes from row half 0 to 1
-  int wave, kt1;          // k steps of this piece
+  uint32_t lds0;          // LDS byte of this wave's rows of slot 0
+  uint32_t slot;          // slot (LDS byte) of the region to read next
+  int kt1;                // k steps of this piece
 
-  __device__ __forceinline__ void read_a(const unsigned char *r) {
+  __device__ __forceinline__ void read_a(const unsigned char *lds) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int m = 0; m < 4; ++m) a[m][ks] = *reinterpret_cast<const bf16x8 *>(r + fa[ks] + m * 16 * 128);
+      for (int m = 0; m < 4; ++m)
+        a[m][ks] = *reinterpret_cast<const bf16x8 *>(lds + (slot + fa[ks]) + m * 16 * 128);
+    slot = slot_after<1>(slot);
   }
-  __device__ __forceinline__ void read_b(bf16x8 (&b)[2][2], const unsigned char *r) {
+  template <int C>
+  __device__ __forceinline__ void read_b(const unsigned char *lds) {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-      for (int n = 0; n < 2; ++n) b[n][ks] = *reinterpret_cast<const bf16x8 *>(r + fb[ks] + n * 16 * 128);
+      for (int n = 0; n < 2; ++n)
+        b[C][n][ks] = *reinterpret_cast<const bf16x8 *>(lds + (slot + fb[ks]) + n * 16 * 128);
+    slot = slot_after<1>(slot);
   }
-  __device__ __forceinline__ void mma(f32x4 (&c)[4][2], const bf16x8 (&b)[2][2]) {
+  template <int HH, int C>
+  __device__ __forceinline__ void mma() {
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
       for (int m = 0; m < 4; ++m)
 #pragma unroll
-        for (int n = 0; n < 2; ++n) c[m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[n][ks], a[m][ks], c[m][n], 0, 0, 0);
+        for (int n = 0; n < 2; ++n)
+          acc[HH][C][m][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(b[C][n][ks], a[m][ks], acc[HH][C][m][n], 0, 0, 0);
   }
-  // Copies of k step kt; steps past the last read nothing and write zeros (no
-  // fragment of them is used), which keeps the count of copies in flight.
-  __device__ __forceinline__ void copy_a(int h, int kt, unsigned char *r) {
-    const uint32_t off = h * a_half + (uint32_t)kt * 128;
-    copy_region(A + off, kt < kt1 && na > off ? na - off : 0, r, wave, va);
+  // Copies of k step kt into the slot at `to`; steps past the last read
+  // nothing and write zeros (no fragment of them is used), which keeps the
+  // count of copies in flight.
+  template <int HH>
+  __device__ __forceinline__ void copy_a(int kt, uint32_t to) {
+    const uint32_t off = HH * a_half + (uint32_t)kt * 128;
+    copy_region(A + off, kt < kt1 && na > off ? na - off : 0, lds0 + to, va);
   }
-  __device__ __forceinline__ void copy_b(int h, int kt, unsigned char *r) {
-    const uint32_t off = (uint32_t)kt * 128, n = h ? nb1 : nb0;
-    copy_region((h ? W1 : W0) + off, kt < kt1 && n > off ? n - off : 0, r, wave, vb);
+  template <int C>
+  __device__ __forceinline__ void copy_b(int kt, uint32_t to) {
+    const uint32_t off = (uint32_t)kt * 128, n = C ? nb1 : nb0;
+    copy_region((C ? W1 : W0) + off, kt < kt1 && n > off ? n - off : 0, lds0 + to, vb);
   }
 };
 
@@ -150,60 +184,56 @@ __device__ __forceinline__ void enter_mma() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// One k step of a 256-row tile, T its parity. A0, A1, B1, B0: this step's
-// regions (B0 was read in the previous step's last phase); A1n, B0n: the next
-// step's.
-template <int T>
-__device__ __forceinline__ void step_full(Tile<2> &s, int kt, unsigned char *A0, unsigned char *A1, unsigned char *B0,
-                                          unsigned char *B1, unsigned char *A1n, unsigned char *B0n) {
-  s.read_a(A0);
-  s.copy_a(1, kt + 1, A1n);
-  enter_mma<10>();
-  s.mma(s.acc[0][0], s.b0[T]);
+// One k step of a 256-row tile. F is the column half of its first and last
+// phase (0 on even steps, 1 on odd ones), whose fragments were read in the
+// previous step's last phase. The regions pass through the ring of slots in the
+// order in which they are read: A half 0, column half 1 - F, A half 1, column
+// half 1 - F of the next step. Phase i copies the region that phase i + 8
+// reads, into the slot whose region phase i - 2 read.
+template <int F>
+__device__ __forceinline__ void step_full(Tile<2> &s, int kt, const unsigned char *lds) {
+  s.copy_a<0>(kt + 2, slot_after<8>(s.slot));
+  s.read_a(lds);
+  enter_mma<14>();
+  s.mma<0, F>();
   phase_barrier();
-  s.read_b(s.b1, B1);
-  s.copy_b(0, kt + 2, B0);
-  enter_mma<10>();
-  s.mma(s.acc[0][1], s.b1);
+  s.copy_b<1 - F>(kt + 2, slot_after<8>(s.slot));
+  s.read_b<1 - F>(lds);
+  enter_mma<14>();
+  s.mma<0, 1 - F>();
   phase_barrier();
-  s.read_a(A1);
-  s.copy_a(0, kt + 2, A0);
-  enter_mma<10>();
-  s.mma(s.acc[1][1], s.b1);
+  s.copy_a<1>(kt + 2, slot_after<8>(s.slot));
+  s.read_a(lds);
+  enter_mma<14>();
+  s.mma<1, 1 - F>();
   phase_barrier();
-  s.read_b(s.b0[T ^ 1], B0n);
-  s.copy_b(1, kt + 2, B1);
-  enter_mma<10>();
-  s.mma(s.acc[1][0], s.b0[T]);
-  phase_barrier();
-}
-
-// One k step of a 128-row tile: A, B1, B0 this step's regions, Ap and B1p the
-// previous step's (= step kt + 2), B0n the next step's.
-__device__ __forceinline__ void step_half(Tile<1> &s, int kt, unsigned char *A, unsigned char *B0, unsigned char *B1,
-                                          unsigned char *Ap, unsigned char *B1p, unsigned char *B0n) {
-  s.read_a(A);
-  s.copy_a(0, kt + 2, Ap);
-  enter_mma<8>();
-  s.mma(s.acc[0][0], s.b0[0]);
-  phase_barrier();
-  s.read_b(s.b1, B1);
-  s.read_b(s.b0[0], B0n);
-  s.copy_b(1, kt + 2, B1p);
-  s.copy_b(0, kt + 3, B0);
-  enter_mma<10>();
-  s.mma(s.acc[0][1], s.b1);
+  s.copy_b<1 - F>(kt + 3, slot_after<8>(s.slot));
+  s.read_b<1 - F>(lds);
+  enter_mma<14>();
+  s.mma<1, F>();
   phase_barrier();
 }
 
-struct Lds {
-  unsigned char *r[9];
-};
+// One k step of a 128-row tile: A; column half 1 and the next step's half 0.
+__device__ __forceinline__ void step_half(Tile<1> &s, int kt, const unsigned char *lds) {
+  s.copy_b<1>(kt + 2, slot_after<7>(s.slot));
+  s.read_a(lds);
+  enter_mma<10>();
+  s.mma<0, 0>();
+  phase_barrier();
+  s.copy_b<0>(kt + 3, slot_after<7>(s.slot));
+  s.copy_a<0>(kt + 3, slot_after<8>(s.slot));
+  s.read_b<1>(lds);
+  s.read_b<0>(lds);
+  enter_mma<12>();
+  s.mma<0, 1>();
+  phase_barrier();
+}
 
 // One tile: rows m0 .. of H 128-row halves, column tile tc, k piece kp.
 template <int H, bool GLU>
 __device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, int unit, int kp, int k_parts,
-                                         const Lds L) {
+                                         unsigned char *lds) {
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
   const int l16 = lane & 15, quad = lane >> 4, wm = wave >> 2, wn = wave & 3;
   int si = 0;
@@ -214,7 +244,8 @@ __device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, 
   const uint32_t rb = (uint32_t)p.j.K * 2;
   const int KT = p.j.K / kTK, k0 = (int)((int64_t)kp * KT / k_parts), k1 = (int)((int64_t)(kp + 1) * KT / k_parts);
   Tile<H> s;
-  s.wave = wave;
+  s.lds0 = (uint32_t)(uintptr_t)(lds_u8 *)lds + wave * 2048;
+  s.slot = 0;
   s.kt1 = k1 - k0;
   const uint32_t ko = (uint32_t)k0 * 128;
   const uint32_t rows = (uint32_t)min((int64_t)128 * H, p.j.M - m0);
@@ -253,49 +284,45 @@ __device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, 
 #pragma unroll
       for (int m = 0; m < 4; ++m) s.acc[h][j][m][0] = s.acc[h][j][m][1] = f32x4{};
 
-  // The copies run in the order in which the phases read the regions. Group 1
-  // then falls half a phase behind; group 0 waits for it at the end.
+  // The first regions in the order in which they are read. Group 1 then falls
+  // half a phase behind; group 0 waits for it at the end.
   int kt = 0;
   if constexpr (H == 2) {
-    // regions 0-3: A0 A1 B0 B1 of even k steps, 4-7 of odd ones
-    s.copy_b(0, 0, L.r[2]);
-    s.copy_a(0, 0, L.r[0]);
-    s.copy_b(1, 0, L.r[3]);
-    s.copy_a(1, 0, L.r[1]);
-    s.copy_b(0, 1, L.r[6]);
-    s.copy_a(0, 1, L.r[4]);
-    s.copy_b(1, 1, L.r[7]);
-    wait_vm<10>();
+    s.template copy_b<0>(0, 0);
+    s.template copy_a<0>(0, kRegion);
+    s.template copy_b<1>(0, 2 * kRegion);
+    s.template copy_a<1>(0, 3 * kRegion);
+    s.template copy_b<1>(1, 4 * kRegion);
+    s.template copy_a<0>(1, 5 * kRegion);
+    s.template copy_b<0>(1, 6 * kRegion);
+    s.template copy_a<1>(1, 7 * kRegion);
+    s.template copy_b<0>(2, 8 * kRegion);
+    wait_vm<14>();
     phase_barrier();
-    s.read_b(s.b0[0], L.r[2]);
+    s.template read_b<0>(lds);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): slot 0 is written again in phase 1
     if (wm) phase_barrier();
     for (;;) {
-      step_full<0>(s, kt, L.r[0], L.r[1], L.r[2], L.r[3], L.r[5], L.r[6]);
+      step_full<0>(s, kt, lds);
       if (++kt == s.kt1) break;
-      step_full<1>(s, kt, L.r[4], L.r[5], L.r[6], L.r[7], L.r[1], L.r[2]);
+      step_full<1>(s, kt, lds);
       if (++kt == s.kt1) break;
     }
   } else {
-    // stage j = k step mod 3: A = region 3j, B0 = 3j + 1, B1 = 3j + 2
-    s.copy_b(0, 0, L.r[1]);
-    s.copy_a(0, 0, L.r[0]);
-    s.copy_b(1, 0, L.r[2]);
-    s.copy_b(0, 1, L.r[4]);
-    s.copy_a(0, 1, L.r[3]);
-    s.copy_b(1, 1, L.r[5]);
-    s.copy_b(0, 2, L.r[7]);
-    wait_vm<10>();
+    s.template copy_b<0>(0, 0);
+    s.template copy_a<0>(0, kRegion);
+    s.template copy_b<1>(0, 2 * kRegion);
+    s.template copy_b<0>(1, 3 * kRegion);
+    s.template copy_a<0>(1, 4 * kRegion);
+    s.template copy_b<1>(1, 5 * kRegion);
+    s.template copy_b<0>(2, 6 * kRegion);
+    s.template copy_a<0>(2, 7 * kRegion);
+    wait_vm<12>();
     phase_barrier();
-    s.read_b(s.b0[0], L.r[1]);
+    s.template read_b<0>(lds);
+    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): slot 0 is written again in phase 1
     if (wm) phase_barrier();
-    for (;;) {
-      step_half(s, kt, L.r[0], L.r[1], L.r[2], L.r[6], L.r[8], L.r[4]);
-      if (++kt == s.kt1) break;
-      step_half(s, kt, L.r[3], L.r[4], L.r[5], L.r[0], L.r[2], L.r[7]);
-      if (++kt == s.kt1) break;
-      step_half(s, kt, L.r[6], L.r[7], L.r[8], L.r[3], L.r[5], L.r[1]);
-      if (++kt == s.kt1) break;
-    }
+    for (; kt < s.kt1; ++kt) step_half(s, kt, lds);
   }
   if (!wm) phase_barrier();
   wait_vm<0>();
@@ -306,9 +333,7 @@ __device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, 
   // (rows of 256 B, gated 128 B, 16-byte chunks XOR-swizzled by row), then
   // each lane finishes 8 consecutive columns of a row, so that residual loads
   // and stores are 16 bytes of whole row segments.
-  unsigned char *stg = L.r[0];
-#pragma unroll
-  for (int w = 1; w < 8; ++w) stg = wave == w ? L.r[w] : stg;
+  unsigned char *stg = lds + wave * kRegion;
   constexpr int CPR = GLU ? 4 : 8;        // lanes (8 columns each) per row
   const int cg = lane % CPR;
   const int n = n0 + wn * (TN / 4) + cg * 8;
@@ -414,11 +439,7 @@ __device__ __forceinline__ void unit_coords(const GemmPlan &p, int u, int64_t &m
 // neighbours in the order share A and W rows in that XCD's L2.
 template <bool GLU>
 __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(const GemmPlan p) {
-  // nine objects, so that the compiler can tell the copies in flight from the
-  // regions being read
-  __shared__ __attribute__((aligned(1024))) unsigned char r0[kRegion], r1[kRegion], r2[kRegion], r3[kRegion],
-      r4[kRegion], r5[kRegion], r6[kRegion], r7[kRegion], r8[kRegion];
-  const Lds L = {{r0, r1, r2, r3, r4, r5, r6, r7, r8}};
+  __shared__ __attribute__((aligned(1024))) unsigned char lds[kLds];
   const int xcd = blockIdx.x % kXcds, slot = blockIdx.x / kXcds;
   const int full_per = (p.n_full + kXcds - 1) / kXcds;
   if (slot < full_per) {
@@ -426,7 +447,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(const GemmPlan p) {
     if (t >= p.n_full) return;
     int tm, tc;
     tile_coords(p, t, tm, tc);
-    run_tile<2, GLU>(p, (int64_t)tm * 256, tc, 0, 0, 1, L);
+    run_tile<2, GLU>(p, (int64_t)tm * 256, tc, 0, 0, 1, lds);
     return;
   }
   const int jobs = p.n_half * p.k_parts, per = (jobs + kXcds - 1) / kXcds;
@@ -436,7 +457,7 @@ __global__ __launch_bounds__(512, 2) void gemm_bf16_kernel(const GemmPlan p) {
   int tc;
   int64_t m0;
   unit_coords(p, u, m0, tc);
-  run_tile<1, GLU>(p, m0, tc, u, i / p.n_half, p.k_parts, L);
+  run_tile<1, GLU>(p, m0, tc, u, i / p.n_half, p.k_parts, lds);
 }
 
 // The cut units' k pieces summed: C = sum of pieces (+ residual) (+ bias), in
