@@ -16,22 +16,26 @@
 //   (rows half 0, columns 0-31), (0, 32-63), (1, 32-63), (1, 0-31)
 // so that only one operand fragment set changes per phase.
 //
-// Both operands are K-contiguous, as the matrix cores take them. LDS holds two
-// k steps as 16 KiB regions of 128 rows x 128 bytes (A rows half 0 / half 1, W
-// columns 0-31 / 32-63 of every wave), 16-byte chunks XOR-swizzled by
-// (row / 2) mod 8: no bank conflicts (SQ_LDS_BANK_CONFLICT = 0). A region is
-// copied again two phases after its fragments were read (by then both groups
-// have read it) and is waited for six phases after its copy was issued with a
-// counted s_waitcnt vmcnt: the five younger copies stay in flight across the
-// barriers. The previous kernel waited for every copy once per k step.
+// Both operands are K-contiguous, as the matrix cores take them. All of the LDS
+// is a ring of ten 16 KiB regions of 128 rows x 128 bytes (A rows half 0 / half
+// 1, W columns 0-31 / 32-63 of every wave), 16-byte chunks XOR-swizzled by
+// (row / 2) mod 8: no bank conflicts (SQ_LDS_BANK_CONFLICT = 0). Regions pass
+// through it in the order in which they are read. A slot is copied into again
+// two phases after its fragments were read (by then both groups have read it),
+// eight phases before its new region is, and that copy is waited for with a
+// counted s_waitcnt vmcnt, the seven younger ones staying in flight across the
+// barriers. (Two k steps of regions and copies six phases ahead: 5-6% slower in
+// a decoder layer, where the weights come from HBM.)
 //
 // What bounds it: the chip's power. At 8192^3 the matrix cores are busy 83% of
 // the cycles, but at a shader clock of 1.5-1.6 GHz; the instruction that needs
 // less power per FLOP runs faster. v_mfma_f32_16x16x32_bf16 reads and writes
-// half the accumulator registers per FLOP of v_mfma_f32_32x32x16_bf16: the
-// same kernel ran 868 us with 32x32x16 and 732 us with 16x16x32 (1502
-// TFLOP/s; the previous 2-stage kernel with 32x32x16 ~1150). 64-byte rows per
-// copy (k steps of 32, four stages) doubled the L2 requests: 911 us.
+// half the accumulator registers per FLOP of v_mfma_f32_32x32x16_bf16: an early
+// form of this kernel ran 868 us with 32x32x16 and 732 us with 16x16x32 (1502
+// TFLOP/s; the previous two-stage kernel with 32x32x16 ~1150). 64-byte rows per
+// copy (k steps of 32, four stages) doubled the L2 requests: 911 us. With few
+// rows it is HBM latency: 986 x 3584 x 18944 takes 168 us with the weights in
+// the caches and 231 us from HBM.
 //
 // Work list (plan_job): whole rounds of 256 tiles, one per CU, then the rest:
 // row ranges of at most 128 rows and, where that shortens the last round,
@@ -39,6 +43,7 @@
 // three LDS stages) and, given a workspace, cut along k, all in the same
 // launch after the whole tiles.
 #include <algorithm>
+#include <type_traits>
 
 #include "daf_internal.h"
 #include "gemm.h"
@@ -83,19 +88,22 @@ __device__ __forceinline__ void phase_barrier() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
-// Copy a region into LDS at byte `lds`: this wave writes rows 16 wave .. 16
-// wave + 15 (two 1 KiB instructions); bytes at or past `nrec` from `base` read
-// as zero. In asm, so that the compiler does not wait for the copies in flight
-// at each LDS read: wait_vm counts them, the phase barriers order them.
-__device__ __forceinline__ void copy_region(const unsigned char *base, uint32_t nrec, uint32_t lds,
-                                            const uint32_t (&voff)[2]) {
-#if defined(__HIP_DEVICE_COMPILE__)
-  const uint64_t a = (uint64_t)base;
+// A region copy: buffer descriptor of the source rows and the LDS byte of this
+// wave's share.
+struct Copy {
   u32x4 r;
-  r[0] = __builtin_amdgcn_readfirstlane((unsigned)a);
-  r[1] = __builtin_amdgcn_readfirstlane((unsigned)(a >> 32) & 0xffffu);
-  r[2] = __builtin_amdgcn_readfirstlane(nrec);
-  r[3] = kRsrcWord3;
+  uint32_t lds;
+};
+__device__ __forceinline__ Copy make_copy(const unsigned char *base, uint32_t nrec, uint32_t lds) {
+  const uint64_t a = (uint64_t)base;
+  return Copy{{(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, nrec, kRsrcWord3}, lds};
+}
+// Issue it: this wave copies rows 16 wave .. 16 wave + 15 (two 1 KiB
+// instructions); bytes at or past the descriptor's extent read as zero. In asm,
+// so that the compiler does not wait for the copies in flight at each LDS read:
+// wait_vm counts them, the phase barriers order them.
+__device__ __forceinline__ void issue(const Copy &c, const uint32_t (&voff)[2]) {
+#if defined(__HIP_DEVICE_COMPILE__)
   asm volatile(
       "s_mov_b32 m0, %0\n\t"
       "s_nop 0\n\t"
@@ -104,7 +112,7 @@ __device__ __forceinline__ void copy_region(const unsigned char *base, uint32_t 
       "s_nop 0\n\t"
       "buffer_load_dwordx4 %3, %4, 0 offen lds"
       :
-      : "s"(lds), "s"(lds + 1024), "v"(voff[0]), "v"(voff[1]), "s"(r)
+      : "s"(c.lds), "s"(c.lds + 1024), "v"(voff[0]), "v"(voff[1]), "s"(c.r)
       : "memory");
 #endif
 }
@@ -160,16 +168,17 @@ struct Tile {
   }
   // Copies of k step kt into the slot at `to`; steps past the last read
   // nothing and write zeros (no fragment of them is used), which keeps the
-  // count of copies in flight.
+  // count of copies in flight. Before that the extents reach past the offset:
+  // a 256-row tile has more than 128 valid rows and a tile at least 64 columns.
   template <int HH>
-  __device__ __forceinline__ void copy_a(int kt, uint32_t to) {
+  __device__ __forceinline__ Copy copy_a(int kt, uint32_t to) const {
     const uint32_t off = HH * a_half + (uint32_t)kt * 128;
-    copy_region(A + off, kt < kt1 && na > off ? na - off : 0, lds0 + to, va);
+    return make_copy(A + off, kt < kt1 ? na - off : 0, lds0 + to);
   }
   template <int C>
-  __device__ __forceinline__ void copy_b(int kt, uint32_t to) {
-    const uint32_t off = (uint32_t)kt * 128, n = C ? nb1 : nb0;
-    copy_region((C ? W1 : W0) + off, kt < kt1 && n > off ? n - off : 0, lds0 + to, vb);
+  __device__ __forceinline__ Copy copy_b(int kt, uint32_t to) const {
+    const uint32_t off = (uint32_t)kt * 128;
+    return make_copy((C ? W1 : W0) + off, kt < kt1 ? (C ? nb1 : nb0) - off : 0, lds0 + to);
   }
 };
 
@@ -184,49 +193,74 @@ __device__ __forceinline__ void enter_mma() {
   __builtin_amdgcn_sched_barrier(0);
 }
 
+// The next phase's copy is prepared (scalar work) between this phase's MFMAs,
+// so that a phase starts with its LDS reads: with the descriptor computed before
+// them a phase took longer than the other group's MFMAs (2586 x 3584 x 18944,
+// 154 workgroups: 327 us, with this 296).
+__device__ __forceinline__ void spread_scalar() {
+#pragma unroll
+  for (int i = 0; i < 16; ++i) {
+    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+    __builtin_amdgcn_sched_group_barrier(0x004, 2, 0);  // scalar
+  }
+}
+
 // One k step of a 256-row tile. F is the column half of its first and last
 // phase (0 on even steps, 1 on odd ones), whose fragments were read in the
 // previous step's last phase. The regions pass through the ring of slots in the
 // order in which they are read: A half 0, column half 1 - F, A half 1, column
 // half 1 - F of the next step. Phase i copies the region that phase i + 8
-// reads, into the slot whose region phase i - 2 read.
+// reads, into the slot whose region phase i - 2 read. n: the first phase's copy.
 template <int F>
-__device__ __forceinline__ void step_full(Tile<2> &s, int kt, const unsigned char *lds) {
-  s.copy_a<0>(kt + 2, slot_after<8>(s.slot));
+__device__ __forceinline__ void step_full(Tile<2> &s, Copy &n, int kt, const unsigned char *lds) {
   s.read_a(lds);
+  issue(n, s.va);
   enter_mma<14>();
+  n = s.copy_b<1 - F>(kt + 2, slot_after<8>(s.slot));
   s.mma<0, F>();
+  spread_scalar();
   phase_barrier();
-  s.copy_b<1 - F>(kt + 2, slot_after<8>(s.slot));
   s.read_b<1 - F>(lds);
+  issue(n, s.vb);
   enter_mma<14>();
+  n = s.copy_a<1>(kt + 2, slot_after<8>(s.slot));
   s.mma<0, 1 - F>();
+  spread_scalar();
   phase_barrier();
-  s.copy_a<1>(kt + 2, slot_after<8>(s.slot));
   s.read_a(lds);
+  issue(n, s.va);
   enter_mma<14>();
+  n = s.copy_b<1 - F>(kt + 3, slot_after<8>(s.slot));
   s.mma<1, 1 - F>();
+  spread_scalar();
   phase_barrier();
-  s.copy_b<1 - F>(kt + 3, slot_after<8>(s.slot));
   s.read_b<1 - F>(lds);
+  issue(n, s.vb);
   enter_mma<14>();
+  n = s.copy_a<0>(kt + 3, slot_after<8>(s.slot));
   s.mma<1, F>();
+  spread_scalar();
   phase_barrier();
 }
 
 // One k step of a 128-row tile: A; column half 1 and the next step's half 0.
-__device__ __forceinline__ void step_half(Tile<1> &s, int kt, const unsigned char *lds) {
-  s.copy_b<1>(kt + 2, slot_after<7>(s.slot));
+__device__ __forceinline__ void step_half(Tile<1> &s, Copy &n, int kt, const unsigned char *lds) {
   s.read_a(lds);
+  issue(n, s.vb);
   enter_mma<10>();
+  n = s.copy_b<0>(kt + 3, slot_after<7>(s.slot));
+  const Copy n2 = s.copy_a<0>(kt + 3, slot_after<8>(s.slot));
   s.mma<0, 0>();
+  spread_scalar();
   phase_barrier();
-  s.copy_b<0>(kt + 3, slot_after<7>(s.slot));
-  s.copy_a<0>(kt + 3, slot_after<8>(s.slot));
   s.read_b<1>(lds);
   s.read_b<0>(lds);
+  issue(n, s.vb);
+  issue(n2, s.va);
   enter_mma<12>();
+  n = s.copy_b<1>(kt + 3, slot_after<7>(s.slot));
   s.mma<0, 1>();
+  spread_scalar();
   phase_barrier();
 }
 
@@ -287,42 +321,44 @@ __device__ __forceinline__ void run_tile(const GemmPlan &p, int64_t m0, int tc, 
   // The first regions in the order in which they are read. Group 1 then falls
   // half a phase behind; group 0 waits for it at the end.
   int kt = 0;
+  auto copy_a = [&](auto h, int k, int slot) { issue(s.template copy_a<decltype(h)::value>(k, slot * kRegion), s.va); };
+  auto copy_b = [&](auto c, int k, int slot) { issue(s.template copy_b<decltype(c)::value>(k, slot * kRegion), s.vb); };
+  constexpr std::integral_constant<int, 0> c0{};
+  constexpr std::integral_constant<int, 1> c1{};
+  copy_b(c0, 0, 0);
+  copy_a(c0, 0, 1);
+  copy_b(c1, 0, 2);
   if constexpr (H == 2) {
-    s.template copy_b<0>(0, 0);
-    s.template copy_a<0>(0, kRegion);
-    s.template copy_b<1>(0, 2 * kRegion);
-    s.template copy_a<1>(0, 3 * kRegion);
-    s.template copy_b<1>(1, 4 * kRegion);
-    s.template copy_a<0>(1, 5 * kRegion);
-    s.template copy_b<0>(1, 6 * kRegion);
-    s.template copy_a<1>(1, 7 * kRegion);
-    s.template copy_b<0>(2, 8 * kRegion);
+    copy_a(c1, 0, 3);
+    copy_b(c1, 1, 4);
+    copy_a(c0, 1, 5);
+    copy_b(c0, 1, 6);
+    copy_a(c1, 1, 7);
+    copy_b(c0, 2, 8);
     wait_vm<14>();
-    phase_barrier();
-    s.template read_b<0>(lds);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): slot 0 is written again in phase 1
-    if (wm) phase_barrier();
+  } else {
+    copy_b(c0, 1, 3);
+    copy_a(c0, 1, 4);
+    copy_b(c1, 1, 5);
+    copy_b(c0, 2, 6);
+    copy_a(c0, 2, 7);
+    wait_vm<12>();
+  }
+  phase_barrier();
+  s.template read_b<0>(lds);
+  __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): slot 0 is written again in phase 1
+  if (wm) phase_barrier();
+  if constexpr (H == 2) {
+    Copy n = s.template copy_a<0>(2, slot_after<8>(s.slot));
     for (;;) {
-      step_full<0>(s, kt, lds);
+      step_full<0>(s, n, kt, lds);
       if (++kt == s.kt1) break;
-      step_full<1>(s, kt, lds);
+      step_full<1>(s, n, kt, lds);
       if (++kt == s.kt1) break;
     }
   } else {
-    s.template copy_b<0>(0, 0);
-    s.template copy_a<0>(0, kRegion);
-    s.template copy_b<1>(0, 2 * kRegion);
-    s.template copy_b<0>(1, 3 * kRegion);
-    s.template copy_a<0>(1, 4 * kRegion);
-    s.template copy_b<1>(1, 5 * kRegion);
-    s.template copy_b<0>(2, 6 * kRegion);
-    s.template copy_a<0>(2, 7 * kRegion);
-    wait_vm<12>();
-    phase_barrier();
-    s.template read_b<0>(lds);
-    __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): slot 0 is written again in phase 1
-    if (wm) phase_barrier();
-    for (; kt < s.kt1; ++kt) step_half(s, kt, lds);
+    Copy n = s.template copy_b<1>(2, slot_after<7>(s.slot));
+    for (; kt < s.kt1; ++kt) step_half(s, n, kt, lds);
   }
   if (!wm) phase_barrier();
   wait_vm<0>();
@@ -504,12 +540,13 @@ __global__ __launch_bounds__(256) void gemm_reduce_kernel(const GemmPlan p) {
 // else 128-row units. Whole rounds of 256 tiles always run whole; the r tiles
 // of a last, partial round run
 //   whole, r + units workgroups:                one tile's time,
-//   as 2 r halves if these fit the CUs:         0.57 of it (a k step of a
-//     128-row tile takes 0.55-0.57 us, of a 256-row tile 0.95-1.0 us while
-//     part of the CUs is busy; K = 18944: 160 against 280 us),
+//   as 2 r halves if these fit the CUs:         0.6-0.65 of it (a k step of
+//     a 128-row tile takes 0.57 us, of a 256-row tile 0.95-1.0 us while part of
+//     the CUs is busy and the weights are in the caches, 0.8 and 1.2 us with
+//     the weights from HBM, as in a program that goes through its layers),
 //   as halves cut into P pieces along k:        1/P of that, plus the fp32
-//     pieces written and read back (128 KiB each, at ~4.5 TB/s for both
-//     passes) and the reduction's launch,
+//     pieces written and read back (128 KiB each) and the reduction's launch
+//     (10 us in all for 224 pieces, and about 4 us more of the tiles' stores),
 // whichever the figures below say is shortest.
 void plan_job(GemmPlan &p, size_t part_bytes) {
   const GemmJob &j = p.j;
@@ -524,8 +561,8 @@ void plan_job(GemmPlan &p, size_t part_bytes) {
   const int edge = rest > 0 && rest <= 128 ? p.tn : 0;  // 128-row units of the last rows
   const int n_tiles = p.tiles_m * p.tn, r = n_tiles % kCus;
   const double kt = j.K / kTK;
-  const double whole_us = 0.97 * kt + 8.0;
-  auto half_us = [&](double k) { return 0.57 * k + 6.0; };
+  const double whole_us = 1.2 * kt + 8.0;
+  auto half_us = [&](double k) { return 0.8 * k + 6.0; };
   p.n_cut = 0;
   p.k_parts = 1;
   const int units = 2 * r + edge;
@@ -533,7 +570,7 @@ void plan_job(GemmPlan &p, size_t part_bytes) {
   if (units > 0 && units <= kCus) {
     for (int parts = 1; parts * units <= kCus && (parts == 1 || 2 * parts <= kt); ++parts) {
       if (parts > 1 && (p.part == nullptr || j.glu || (size_t)units * parts * 128 * 256 * 4 > part_bytes)) break;
-      const double us = half_us(kt / parts) + (parts > 1 ? 5.0 + units * parts * 0.058 : 0.0);
+      const double us = half_us(kt / parts) + (parts > 1 ? 5.0 + units * parts * 0.04 : 0.0);
       if (us < best) {
         best = us;
         p.n_cut = r;
