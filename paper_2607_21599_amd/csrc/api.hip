@@ -969,8 +969,7 @@ daf_status_t daf_decoder_layer(const daf_attn_cfg_t *cfg, const daf_layer_weight
       g.seg[g.n_segs++] = GemmSeg{w->wv, w->bv, v, KW};
       CHECK(run_gemm(g, stream, part));
     }
-    hipError_t e1 = launch_rope(R, c.hq, c.d, QW, q, pos, w->rope_theta, stream);
-    if (e1 == hipSuccess) e1 = launch_rope(R, c.hkv, c.d, KW, k, pos, w->rope_theta, stream);
+    const hipError_t e1 = launch_rope(R, c.hq, c.d, QW, q, pos, w->rope_theta, stream, c.hkv, KW, k);
     if (e1 != hipSuccess) return hip_fail(e1, "rope launch");
     if (mode == DAF_LAYER_DAF) {
       const int64_t ni = b.total_imp;

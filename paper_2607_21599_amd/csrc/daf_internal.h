@@ -174,8 +174,9 @@ hipError_t launch_select_topn(const SelectLaunch &p, hipStream_t st);
 // ---- row-wise pieces of the decoder layer ------------------------------------
 hipError_t launch_rmsnorm(int64_t rows, int width, const void *x, const void *w, float eps, void *y,
                           hipStream_t st);
+// x2: optional second tensor of the same rows and head size (q and k in one launch)
 hipError_t launch_rope(int64_t rows, int heads, int d, int64_t row_stride, void *x, const int32_t *pos,
-                       double theta, hipStream_t st);
+                       double theta, hipStream_t st, int heads2 = 0, int64_t row_stride2 = 0, void *x2 = nullptr);
 hipError_t launch_silu_mul(int64_t rows, int width, const void *gu, void *out, hipStream_t st);
 
 }  // namespace daf

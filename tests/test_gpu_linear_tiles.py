@@ -1,4 +1,5 @@
-"""GPU: the projections at the edges of their tiling, against the CPU oracle.
+"""GPU: the projections at the edges of their tiling, and the rotary embedding on
+either side of its vector rule, against the CPU oracle.
 
 256-row and 128-row tiles, ragged last rows on either side of 128, column
 counts that end inside a 256-column tile, one, odd and even k step counts, and
@@ -62,3 +63,26 @@ def test_swiglu_tiles(M, I, K):
     ref = dec.silu_mul(dec.linear(w(A), w(Wgu)[:I]), dec.linear(w(A), w(Wgu)[I:]))
     _check(C[:M], ref, f"swiglu {M}x{I}x{K}")
     assert torch.all(C[M:] == 5.0), "rows past M were written"
+
+
+@pytest.mark.parametrize("rows,heads,d,stride,shift", [
+    (1, 1, 16, 16, 0), (5, 3, 64, 192, 0), (257, 28, 128, 4608, 0), (9, 2, 256, 520, 0),  # 16-byte pieces
+    (7, 3, 64, 196, 0), (6, 2, 128, 256, 1), (3, 2, 24, 48, 0), (4, 1, 512, 512, 0)])     # stride, address, sizes
+def test_rope_paths(rows, heads, d, stride, shift):
+    """Both rope kernels on either side of the rule that picks them; the rest
+    of each row (and what lies before and after) stays."""
+    import paper_2607_21599_amd as daf
+    rng = np.random.Generator(np.random.PCG64(rows + d))
+    raw = di.f32_to_bf16_bits(rng.standard_normal(rows * stride + 16, dtype=np.float32))
+    pos = np.sort(rng.choice(131072, rows, replace=False)).astype(np.int32)
+    t = _dev(raw)
+    daf.daf_rope(rows, heads, d, stride, t[shift:], _dev(pos), 1e6)
+    torch.cuda.synchronize()
+    got = t.view(torch.int16).cpu().numpy().view(np.uint16)
+    x = raw[shift:shift + rows * stride].reshape(rows, stride)
+    ref = dec.rope(di.raw_to_f32(x)[:, :heads * d].reshape(rows, heads, d), pos, 1e6).reshape(rows, heads * d)
+    g = got[shift:shift + rows * stride].reshape(rows, stride)
+    err = np.abs(di.raw_to_f32(g)[:, :heads * d].astype(np.float64) - ref)
+    assert (err <= 2.0 ** -8 * np.abs(ref) + 2e-3).all(), err.max()
+    assert np.array_equal(g[:, heads * d:], x[:, heads * d:]), "past the heads"
+    assert np.array_equal(got[:shift], raw[:shift]) and np.array_equal(got[shift + rows * stride:], raw[shift + rows * stride:])
