@@ -58,8 +58,8 @@
  * Asynchrony. Work is enqueued on `stream` (NULL = the default stream) and the
  *   call returns without synchronising. Calls are re-entrant and thread-safe;
  *   the only state the library keeps is daf_layer_attn's second stream and its
- *   two events per device (created on first use, guarded by a mutex; small
- *   layers use none of them). Calls that write the same buffers must be ordered
+ *   two events per device (created on first use, guarded by a mutex; used by
+ *   batches too large for one attention launch). Calls that write the same buffers must be ordered
  *   by the caller.
  * Graph capture. The calls enqueue kernels and event record/wait operations
  *   only (no allocation, copy, memset or synchronisation), so a sequence of
@@ -236,9 +236,9 @@ size_t daf_layer_workspace_size(const daf_attn_cfg_t *cfg,
 /* One DAF attention layer (Sec. 2 items 1-3), in the order the paper fixes:
  * hybrid KV write-back (DAF_FUSE_KV) first, then stage 2 (with its split
  * merge); stage 1 needs none of these and runs beside them: in the same launch
- * as stage 2 for small layers, else on a stream the library owns (one per
- * device, default priority), forked from `stream` and joined back into it with
- * events. All of the call's work is ordered on `stream` for the caller. Arguments as in the stage calls. o_imp and o_q
+ * as stage 2, or for more than 16 requests on a stream the library owns (one
+ * per device, default priority), forked from `stream` and joined back into it
+ * with events. All of the call's work is ordered on `stream` for the caller. Arguments as in the stage calls. o_imp and o_q
  * receive the stage outputs; the same rows are written into `hidden` exactly
  * as DAF_FUSE_HIDDEN would (the state fusion happens in the stage epilogues,
  * without a separate pass). */

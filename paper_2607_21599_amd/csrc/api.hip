@@ -350,15 +350,16 @@ daf_status_t run_entries(const Cfg &c, AttnKind kind, const std::vector<AttnEntr
   return DAF_OK;
 }
 
-// Whether the layer call runs both stages in one launch: stage 1 is small
-// (kNarrowJobs) and the work tables fit one launch. Such a layer is bound by
-// launches and by the longest chain of key tiles, which the other stage's
-// workgroups then run beside; the second stream's two events and waits cost
-// about 20 us of host time. Layers above the line fill the chip with each
-// stage, and one launch for both was slower than two (287-304 against 277 us at
-// 32k).
+// Whether the layer call runs both stages in one launch: their work tables fit
+// it (at most 16 requests with both stages). One launch needs no second stream
+// (two events and two waits, about 20 us of host time and 6 + 5 us between
+// kernels), and the jobs of one stage fill in where the other's leave CUs idle:
+// 16k keys, n = 2458: 120 us on two streams, 105 in one launch; 32k, n = 4915
+// 261 and 251; eight requests 872 and 869. The fp32 kernel takes its small
+// layers so.
 bool one_launch(const Cfg &c, const std::vector<AttnEntry> &self, const std::vector<AttnEntry> &qdoc) {
   if (self.empty() || qdoc.empty() || self.size() + qdoc.size() > (size_t)kMaxEntries) return false;
+  if (c.dtype == DAF_BF16) return true;
   int64_t jobs = 0;
   for (const AttnEntry &e : self) jobs += (int64_t)e.mb_count * c.hq;
   return jobs <= kNarrowJobs;

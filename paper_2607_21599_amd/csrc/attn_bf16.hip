@@ -603,10 +603,10 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_bf16_kernel(const AttnLa
   }
 }
 
-// Both stages in one launch, for small layers (64-row blocks in stage 1, the
-// longest chains of key tiles first). QDOC_FIRST: the first workgroups of each
-// XCD run stage 2 and the rest stage 1, else the other way round.
-template <int D, bool QDOC_FIRST>
+// Both stages in one launch, one job per workgroup, each stage's heaviest jobs
+// first. QDOC_FIRST: the first workgroups of each XCD run stage 2 and the rest
+// stage 1, else the other way round.
+template <int D, bool QDOC_FIRST, int NB>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_both_kernel(const AttnLaunch p) {
   constexpr int TILE = Geo<D>::TILE;
   __shared__ __attribute__((aligned(1024))) unsigned char k_lds0[TILE];
@@ -616,7 +616,7 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_both_kernel(const AttnLa
   const int xcd = blockIdx.x % kXcds, u = blockIdx.x / kXcds;
   const int n1 = QDOC_FIRST ? 0 : p.list[0].slots_per_xcd, n2 = QDOC_FIRST ? p.list[1].slots_per_xcd : 0;
   const bool self = QDOC_FIRST ? u >= n2 : u < n1;
-  if (self) attn_job<D, 0, 1>(p, p.list[0], xcd, u - n2, k_lds0, v_lds0, k_lds1, v_lds1);
+  if (self) attn_job<D, 0, NB>(p, p.list[0], xcd, u - n2, k_lds0, v_lds0, k_lds1, v_lds1);
   else attn_job<D, 1, 2>(p, p.list[1], xcd, u - n1, k_lds0, v_lds0, k_lds1, v_lds1);
 }
 
@@ -684,20 +684,41 @@ hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
 template <int D>
 hipError_t launch_both_t(const AttnLaunch &p0, hipStream_t st) {
   AttnLaunch p = p0;
-  narrow_blocks(p, p.list[0]);
+  AttnList &l1 = p.list[0], &l2 = p.list[1];
+  const bool narrow = l1.n_groups * p.group <= kNarrowJobs;
+  if (narrow) narrow_blocks(p, l1);
   for (AttnList &l : p.list) l.slots_per_xcd = list_slots(p, l);
-  // The stage with the longer jobs first. A stage-2 tile (32 rows a wave, every
-  // slot taken) costs more than a stage-1 tile, whose shorter blocks also fill
-  // in behind: stage 2 first from a quarter of stage 1's longest chain. Layer,
-  // stage 1 / stage 2 first: 16k keys, n = 819, 128 rows (13 and 14 tiles) 62.3
-  // / 57.1 us; 32k, n = 1638, 16 rows (26 and 8) 67.1 / 62.9; 6k, n = 922, 64
-  // rows (15 and 3) 38.7 / 39.4.
-  int chain1 = 0, chain2 = 0;
-  for (int i = 0; i < p.list[0].n_entries; ++i) chain1 = std::max(chain1, (p.e[i].n_keys + kBN - 1) / kBN);
-  for (int i = 0; i < p.list[1].n_entries; ++i) chain2 = std::max(chain2, p.e[p.list[1].e0 + i].split_keys / kBN);
-  const dim3 grid(kXcds * (p.list[0].slots_per_xcd + p.list[1].slots_per_xcd)), block(kAttnThreads);
-  if (4 * chain2 > chain1) attn_both_kernel<D, true><<<grid, block, 0, st>>>(p);
-  else attn_both_kernel<D, false><<<grid, block, 0, st>>>(p);
+  // Which stage's jobs go first, from an estimate of the time in key tiles of a
+  // 32-row wave (a 16-row wave's takes about 0.6) over the 512 resident
+  // workgroups: all the work spread evenly, or stage 1's longest job, which
+  // waits for a stage-2 job if those go first and take the slots. Stage 2 first ends with stage
+  // 1's lightest blocks, stage 1 first with whole stage-2 jobs (most of one
+  // job's time is lost there). Layer, stage 1 / stage 2 first: 16k keys, n =
+  // 819, 128 question rows 62.3 / 57.1 us; n = 2458 104.9 / 111.8; 32k, n =
+  // 4915 253.9 / 250.7; 6k, n = 922, 64 rows (half the slots) 36.8 / 35.6.
+  const double tile1 = narrow ? 0.6 : 1.0;
+  const int rows = narrow ? 64 : kAttnBM;
+  double work = 0, chain1 = 0, chain2 = 0;
+  for (int i = l1.e0; i < l1.e0 + l1.n_entries; ++i) {
+    const AttnEntry &e = p.e[i];
+    const double tiles = (double)e.n_keys / kBN;
+    chain1 = std::max(chain1, tile1 * tiles);
+    work += tile1 * p.hq * e.mb_count * 0.5 * (tiles + (double)rows / kBN);
+  }
+  for (int i = l2.e0; i < l2.e0 + l2.n_entries; ++i) {
+    const AttnEntry &e = p.e[i];
+    const double tiles = (double)e.split_keys / kBN;
+    chain2 = std::max(chain2, tiles);
+    work += (double)p.hkv * e.mb_count * e.n_splits * tiles;
+  }
+  const double even = work / kTargetWorkgroups;
+  const double wait = kXcds * l2.slots_per_xcd > kTargetWorkgroups * 3 / 4 ? chain2 : 0.0;
+  const bool qdoc_first = std::max(wait + chain1, even) < std::max(chain1, even + 0.75 * chain2);
+  const dim3 grid(kXcds * (l1.slots_per_xcd + l2.slots_per_xcd)), block(kAttnThreads);
+  if (qdoc_first && narrow) attn_both_kernel<D, true, 1><<<grid, block, 0, st>>>(p);
+  else if (qdoc_first) attn_both_kernel<D, true, 2><<<grid, block, 0, st>>>(p);
+  else if (narrow) attn_both_kernel<D, false, 1><<<grid, block, 0, st>>>(p);
+  else attn_both_kernel<D, false, 2><<<grid, block, 0, st>>>(p);
   return hipGetLastError();
 }
 

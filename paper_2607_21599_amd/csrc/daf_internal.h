@@ -153,10 +153,10 @@ hipError_t launch_attention(int dtype, int head_dim, AttnKind kind,
                             const AttnLaunch &p, hipStream_t s);
 hipError_t launch_attention_bf16(int head_dim, AttnKind kind, const AttnLaunch &p,
                                  hipStream_t s);
-// Stage 1 (list[0], at most kNarrowJobs blocks) and stage 2 (list[1]) in one launch (bf16).
+// Stage 1 (list[0]) and stage 2 (list[1]) in one launch (bf16).
 hipError_t launch_attention_both_bf16(int head_dim, const AttnLaunch &p, hipStream_t s);
 // Causal self attention of at most this many 128-row blocks times heads runs
-// 64-row blocks (attn_bf16.hip), and the layer call runs both stages in one launch.
+// 64-row blocks (attn_bf16.hip).
 constexpr int kNarrowJobs = 448;
 hipError_t launch_merge(int dtype, int head_dim, const MergeLaunch &p,
                         hipStream_t s);

@@ -66,9 +66,10 @@ def test_stage1_reference_raised_late(n):
     ([(900, 33, 200), (500, 5, 130)], 4, 1, 64, di.F32),
     ([(700, 20, 90)], 14, 2, 128, di.F32),
     ([(200 + 10 * i, 3 + i, 20 + i) for i in range(20)], 7, 1, 128, di.BF16),  # 40 entries: two launches
-    ([(2100, 16, 2048)], 28, 4, 128, di.BF16), ([(2100, 16, 2049)], 28, 4, 128, di.BF16)])  # the rule's line
+    ([(2100, 16, 2048)], 28, 4, 128, di.BF16), ([(2100, 16, 2049)], 28, 4, 128, di.BF16),  # the rule's line
+    ([(9000, 130, 2300)], 28, 4, 128, di.BF16), ([(30000, 97, 2300), (700, 3, 65)], 28, 4, 128, di.BF16)])
 def test_layer_equals_stage_calls(reqs, hq, hkv, d, dtype):
-    """The layer call in either launch form writes what the stage calls write,
+    """The layer call in each launch form writes what the stage calls write,
     bit for bit, and the stage calls' outputs are the oracle's."""
     from paper_2607_21599_amd.tensors import LayerBuffers
     shapes = [di.Shape(f"l{i}", L_d=r[0], L_q=r[1], n=r[2], hq=hq, hkv=hkv, d=d, dtype=dtype, seed=700 + i)
