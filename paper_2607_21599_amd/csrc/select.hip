@@ -10,19 +10,27 @@
 // bytes read per row); every lane loads 16-byte pieces of the row for all
 // layers before reducing, fp32 sums of squares, a wave reduction per layer.
 //
-// select_topn_kernel: one 1024-thread workgroup per request, the keys held in
-// registers (32 per lane, slab by slab beyond 32k tokens). Scores are
-// non-negative floats, so their bit patterns order like the values: a radix
-// select over 8-bit digits finds the key T of the n-th highest score and how
-// many tokens scoring exactly T to keep. The digit histogram is kept in 32
-// copies, one per lane of a half wave (rows padded to 257 words so that one
-// digit's copies sit in different banks): scores cluster, and with a single
-// copy the lanes of one instruction that share a digit serialise on its word. The passes start below the bits that
-// the lowest and highest key share, so the first histogram spreads over the
-// scores' actual range, and stop early once a digit's keys are all taken.
+// select_topn_kernel: one 1024-thread workgroup per request, its keys held in
+// LDS (slab by slab beyond 32k tokens), copied there without passing through
+// registers. Scores are non-negative floats, so their bit patterns order like
+// the values: a radix select finds the key T of the n-th highest score and how
+// many tokens scoring exactly T to keep, 8 bits per pass of the keys' distance
+// from the lowest one (so the first histogram spreads over the scores' actual
+// range), stopping early once a digit's keys are all taken. The histogram is
+// kept in 16 copies, one per lane modulo 16 (rows padded to 257 words so that
+// one digit's copies sit in different banks): scores cluster, and with a single
+// copy the lanes of one instruction that share a digit serialise on its word.
 // Each wave owns a contiguous range of tokens; a prefix sum over the waves of
 // their kept counts, then ballots within each wave, place every kept index, so
 // the output comes out sorted.
+//   One CU does a request's work and runs each part of the code once or a few
+// times, so it is bound by latencies: of memory (a request's 128 KiB take about
+// 4 us to reach the CU), of the LDS behind each key, and of the instructions
+// themselves, which is why the loops are rolled. Score and top-n together, us,
+// with the keys in registers and straight code before: 1024 tokens 18.3, now
+// 11.4; 8192 26.7 and 18.4; 32768 56.4 and 53.8; 131072 (one layer) 124 and 116;
+// four requests of 3000 to 32768 37.5 and 36.2. Ranking the last 512 keys against
+// each other instead of the last passes cost 4 us more than the passes at 32768.
 #include "daf_internal.h"
 
 namespace daf {
@@ -35,7 +43,8 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kScoreThreads = 256;
 constexpr int kTopnThreads = 1024;
 constexpr int kTopnWaves = kTopnThreads / 64;
-constexpr int kHistCopies = 32, kHistStride = 257;
+constexpr int kChunk = 8;  // keys per lane read from LDS ahead of their use
+constexpr int kHistCopies = 16, kHistStride = 257;
 
 __device__ __forceinline__ float wave_sum(float x) {
 #pragma unroll
@@ -104,8 +113,7 @@ __global__ __launch_bounds__(kScoreThreads) void select_score_kernel(const Selec
   if (lane == 0) p.scores[row] = acc / (float)p.n_layers;
 }
 
-// Requests up to kSlabKeys tokens are held in registers whole (32 keys per
-// lane); longer ones are streamed through 16k-token slabs, reloaded per pass.
+// Keys in LDS at a time (128 KiB); a longer request is reloaded per pass.
 constexpr int kSlabKeys = kTopnThreads * 32;
 
 // Exclusive prefix sum over the waves of a wave-uniform value, in wave order;
@@ -141,54 +149,68 @@ __device__ __forceinline__ int block_scan(int v, int *wsum) {
 }
 
 // Number of set bits of m below this lane.
-__device__ __forceinline__ int lanes_below(unsigned long long m) {
-  return (int)__builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
+__device__ __forceinline__ unsigned lanes_below(unsigned long long m) {
+  return __builtin_amdgcn_mbcnt_hi((unsigned)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)m, 0u));
 }
 
 __device__ __forceinline__ unsigned long long ballot(bool x) { return __builtin_amdgcn_ballot_w64(x); }
 
-// KPL keys per lane; MULTI: a request may span more than one slab.
-template <int KPL, bool MULTI>
+__device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectLaunch p) {
-  constexpr int kSlab = kTopnThreads * KPL, kWaveSlab = kSlab / kTopnWaves;
+  __shared__ unsigned s_key[kSlabKeys + (kChunk - 1) * 64];
   __shared__ int hist[kHistCopies * kHistStride];
   __shared__ int wsum[kTopnWaves];
-  __shared__ unsigned s_lo[kTopnWaves], s_hi[kTopnWaves], s_prefix;
+  __shared__ unsigned s_lo[kTopnWaves], s_hi[kTopnWaves], s_base;
   __shared__ int s_remaining, s_top;
   const int b = blockIdx.x;
   const int L = p.req[b].L_d, n = p.req[b].n;
   if (n <= 0 || L <= 0) return;
   const unsigned *key = reinterpret_cast<const unsigned *>(p.scores + p.req[b].doc0);
   int32_t *out = p.idx + p.req[b].imp0;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int n_slabs = MULTI ? (L + kSlab - 1) / kSlab : 1;
+  const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
+  const int n_slabs = (L - 1) / kSlabKeys + 1;
 
-  // slab s: wave w owns keys s*kSlab + w*kWaveSlab + [0, kWaveSlab); its lane
-  // holds key j*64 + lane of that range in k[j]
-  unsigned k[KPL];
-  int slab_base = 0;  // first key of the wave's range in the loaded slab
-  int lane_end = 0;   // key j of this lane is a token when j * 64 < lane_end
+  // a slab's keys are dealt to the waves in ranges of `steps` * 64, the same in
+  // every slab: a wave copies and reads its own range only, so the passes need no
+  // barrier around a slab
+  const int steps = (min(L, kSlabKeys) + kTopnThreads - 1) / kTopnThreads, own = wave * steps * 64;
+  int slab0 = 0, len = 0;  // first key and keys of the loaded slab
   auto load = [&](int s) {
-    slab_base = s * kSlab + wave * kWaveSlab;
-    lane_end = L - slab_base - lane;
+    slab0 = s * kSlabKeys;
+    len = min(L - slab0, kSlabKeys);
+    for (int j = 0; j < steps; ++j) {
+      // lanes past the last key copy it again; every use below tests the index
+      const unsigned *from = key + slab0 + min(own + j * 64 + lane, len - 1);
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)from,
+                                       (__attribute__((address_space(3))) void *)&s_key[own + j * 64], 4, 0, 0);
+    }
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  // f(key, its index in the wave's range, whether it is a token), in order. The
+  // reads of a chunk are issued together: behind f's LDS atomics and stores each
+  // would wait for the one before. Rolled over chunks: every pass runs once or
+  // a few times, and straight code would wait for its own instructions.
+  auto each = [&](auto f) {
+    const int end = min(steps * 64, len - own);
+    for (int j = 0; j < steps; j += kChunk) {
+      unsigned k[kChunk];
 #pragma unroll
-    for (int j = 0; j < KPL; ++j) {
-      const int i = slab_base + j * 64 + lane;
-      k[j] = i < L ? key[i] : 0u;
+      for (int e = 0; e < kChunk; ++e) k[e] = s_key[own + (j + e) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < kChunk; ++e) f(k[e], (j + e) * 64 + lane, (j + e) * 64 + lane < end);
     }
   };
-  auto valid = [&](int j) { return j * 64 < lane_end; };
 
-  // ---- bits common to every key: the radix passes start below them ----------
+  // ---- the keys' range -------------------------------------------------------
+  for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kTopnThreads) hist[i] = 0;
   unsigned lo = 0xffffffffu, hi = 0u;
   for (int s = 0; s < n_slabs; ++s) {
     load(s);
-#pragma unroll
-    for (int j = 0; j < KPL; ++j)
-      if (valid(j)) {
-        lo = min(lo, k[j]);
-        hi = max(hi, k[j]);
-      }
+    each([&](unsigned k, int, bool token) {
+      lo = min(lo, token ? k : 0xffffffffu);
+      hi = max(hi, token ? k : 0u);
+    });
   }
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
@@ -199,28 +221,30 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
     s_lo[wave] = lo;
     s_hi[wave] = hi;
   }
-  for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kTopnThreads) hist[i] = 0;
   __syncthreads();
 #pragma unroll
   for (int w = 0; w < kTopnWaves; ++w) {
     lo = min(lo, s_lo[w]);
     hi = max(hi, s_hi[w]);
   }
-  // undecided low bits: keys agree on every bit at or above `top`
-  int top = lo == hi ? 0 : 32 - __builtin_clz(lo ^ hi);
-  unsigned prefix = lo & (top == 32 ? 0u : ~((1u << top) - 1u));
-  int remaining = n;  // keys still to take among those matching prefix above `top`
+  // the keys that may hold T: base + [0, 2^top); `remaining` of them are to be
+  // taken, and every key above them
+  unsigned base = (unsigned)uniform((int)lo);
+  const unsigned range = (unsigned)uniform((int)hi) - base;
+  int top = range == 0u ? 0 : 32 - __builtin_clz(range);
+  int remaining = n;
 
-  // ---- radix select of the n-th highest key, 8 bits per pass -----------------
+  // ---- radix select of the n-th highest key, 8 bits per pass -------------------
   while (top > 0) {
     const int w = min(8, top), shift = top - w;
-    const unsigned decided = top == 32 ? 0u : ~0u << top;  // bits matched against prefix
+    const unsigned last = ~0u >> (32 - top);
+    int *mine = &hist[(lane & (kHistCopies - 1)) * kHistStride];
     for (int s = 0; s < n_slabs; ++s) {
-      if (MULTI) load(s);
-#pragma unroll
-      for (int j = 0; j < KPL; ++j)
-        if (valid(j) && ((k[j] ^ prefix) & decided) == 0u)
-          atomicAdd(&hist[(lane & (kHistCopies - 1)) * kHistStride + ((k[j] >> shift) & ((1u << w) - 1u))], 1);
+      if (n_slabs > 1) load(s);
+      each([&](unsigned k, int, bool token) {
+        const unsigned r = k - base;
+        if (token & (r <= last)) atomicAdd(&mine[r >> shift], 1);
+      });
     }
     __syncthreads();
     // digits from the highest down: the selected one holds the remaining-th key
@@ -228,7 +252,7 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
     const int d = (1 << w) - 1 - (int)threadIdx.x;
     int h = 0;
     if (d >= 0) {
-#pragma unroll 8
+#pragma unroll
       for (int c = 0; c < kHistCopies; ++c) {
         h += hist[c * kHistStride + d];
         hist[c * kHistStride + d] = 0;  // cleared for the next pass
@@ -236,56 +260,59 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
     }
     const int above = block_scan(h, wsum);
     if (d >= 0 && above < remaining && above + h >= remaining) {
-      s_prefix = prefix | ((unsigned)d << shift);
+      s_base = base + ((unsigned)d << shift);
       // every key in the digit is taken: no lower bits need deciding
       s_top = above + h == remaining ? 0 : shift;
       s_remaining = above + h == remaining ? 0x7fffffff : remaining - above;
     }
     __syncthreads();
-    prefix = s_prefix;
-    top = s_top;
-    remaining = s_remaining;
+    base = (unsigned)uniform((int)s_base);
+    top = uniform(s_top);
+    remaining = uniform(s_remaining);
   }
-  const unsigned T = prefix;  // keep keys above T and the first `remaining` equal to T
+  const unsigned T = base;  // keep keys above T and the first `remaining` equal to T
 
-  // ---- ordered compaction, slab by slab --------------------------------------
-  int out_base = 0, eq_base = 0;  // kept and equal-to-T keys of earlier slabs
+  // ---- ordered compaction, slab by slab ----------------------------------------
+  int out_base = 0;  // kept keys of earlier slabs
   for (int s = 0; s < n_slabs; ++s) {
-    if (MULTI) load(s);
+    if (n_slabs > 1) load(s);
     int n_gt = 0, n_eq = 0;
-#pragma unroll
-    for (int j = 0; j < KPL; ++j) {
-      n_gt += __popcll(ballot(valid(j) && k[j] > T));
-      n_eq += __popcll(ballot(valid(j) && k[j] == T));
-    }
-    int eq_total, kept_total;
-    const int eq_before = eq_base + wave_scan(n_eq, wsum, eq_total);
+    each([&](unsigned k, int, bool token) {
+      n_gt += __popcll(ballot(token) & ballot(k > T));
+      n_eq += __popcll(ballot(token) & ballot(k == T));
+    });
+    // both counts of a slab are at most 2^15: one scan takes them side by side
+    int totals;
+    const unsigned before = (unsigned)wave_scan((int)((unsigned)n_gt << 16 | (unsigned)n_eq), wsum, totals);
+    const int eq_before = uniform((int)(before & 0xffffu));
     const int eq_keep = max(0, min(n_eq, remaining - eq_before));
-    int pos = out_base + wave_scan(n_gt + eq_keep, wsum, kept_total);
-    if (eq_keep == 0) {
-      // no key equal to T to take in this wave (the usual case): keep the keys above T
-#pragma unroll
-      for (int j = 0; j < KPL; ++j) {
-        const bool keep = valid(j) && k[j] > T;
-        const unsigned long long km = ballot(keep);
-        if (keep) out[pos + lanes_below(km)] = slab_base + j * 64 + lane;
+    int pos = out_base + uniform((int)(before >> 16)) + min(eq_before, remaining);
+    // (a scalar base and a 32-bit lane offset for the stores)
+    if (eq_keep == 0 || (eq_keep == n_eq && T > 0u)) {
+      // none or all of the wave's keys equal to T (the usual case): one comparison
+      const unsigned below = eq_keep == 0 ? T : T - 1u;
+      each([&](unsigned k, int i, bool token) {
+        const bool keep = token & (k > below);
+        const unsigned long long km = ballot(token) & ballot(k > below);
+        char *to = reinterpret_cast<char *>(out + pos);
+        if (keep) *reinterpret_cast<int32_t *>(to + lanes_below(km) * 4u) = slab0 + own + i;
         pos += __popcll(km);
-      }
+      });
     } else {
-      int eq_seen = 0;
-#pragma unroll
-      for (int j = 0; j < KPL; ++j) {
-        const bool v = valid(j);
-        const unsigned long long eq = ballot(v && k[j] == T);
-        const bool keep = (v && k[j] > T) || ((eq >> lane & 1ull) && eq_seen + lanes_below(eq) < eq_keep);
+      int eq_left = eq_keep;  // keys equal to T still to take
+      each([&](unsigned k, int i, bool token) {
+        const unsigned long long eq = ballot(token) & ballot(k == T);
+        const bool keep = token & ((k > T) | ((k == T) & ((int)lanes_below(eq) < eq_left)));
+        eq_left -= min(eq_left, (int)__popcll(eq));
         const unsigned long long km = ballot(keep);
-        if (keep) out[pos + lanes_below(km)] = slab_base + j * 64 + lane;
+        char *to = reinterpret_cast<char *>(out + pos);
+        if (keep) *reinterpret_cast<int32_t *>(to + lanes_below(km) * 4u) = slab0 + own + i;
         pos += __popcll(km);
-        eq_seen += __popcll(eq);
-      }
+      });
     }
-    out_base += kept_total;
-    eq_base += eq_total;
+    const int eq_total = uniform((int)((unsigned)totals & 0xffffu));
+    out_base += uniform((int)((unsigned)totals >> 16)) + min(eq_total, remaining);
+    remaining -= min(eq_total, remaining);
   }
 }
 
@@ -310,10 +337,7 @@ hipError_t launch_select_scores(const SelectLaunch &p, bool bf16, hipStream_t st
 
 hipError_t launch_select_topn(const SelectLaunch &p, hipStream_t st) {
   if (p.n_req <= 0) return hipSuccess;
-  int longest = 0;
-  for (int b = 0; b < p.n_req; ++b) longest = std::max(longest, p.req[b].L_d);
-  if (longest > kSlabKeys) select_topn_kernel<16, true><<<p.n_req, kTopnThreads, 0, st>>>(p);
-  else select_topn_kernel<32, false><<<p.n_req, kTopnThreads, 0, st>>>(p);
+  select_topn_kernel<<<p.n_req, kTopnThreads, 0, st>>>(p);
   return hipGetLastError();
 }
 
