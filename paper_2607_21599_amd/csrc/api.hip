@@ -207,7 +207,8 @@ WsLayout ws_layout(const Cfg &c, const Batch &b, const std::vector<Split> &sp) {
 }
 
 // ---- second stream for the layer call ----------------------------------------
-// daf_layer_attn runs a large stage 1 on a library-owned stream (default priority),
+// When one launch cannot hold both stages' work tables, daf_layer_attn runs
+// stage 1 on a library-owned stream (default priority),
 // forked from and joined back into the caller's stream by events, so that it
 // overlaps the KV write-back, stage 2 and the merge. One stream and two events
 // per device, created on first use; the mutex keeps each call's fork and join
@@ -546,8 +547,8 @@ daf_status_t check_fuse_ptrs(const Batch &b, uint32_t flags, const int32_t *idx,
 }
 
 // The layer's attention: hybrid KV write-back, stage 2 with its merge, and
-// stage 1 (on the second stream); with `hidden` set, the stage epilogues also
-// fuse the outputs into it. Pointers are checked by the caller.
+// stage 1 (in stage 2's launch, or on the second stream); with `hidden` set, the
+// stage epilogues also fuse the outputs into it. Pointers are checked by the caller.
 daf_status_t layer_attn_impl(const Cfg &c, const Batch &b, const int32_t *idx, const void *q_imp,
                              const void *k_imp, const void *v_imp, const void *q_q, const void *k_q,
                              const void *v_q, void *k_cache, void *v_cache, void *o_imp, float *lse_imp, void *o_q,
@@ -564,7 +565,7 @@ daf_status_t layer_attn_impl(const Cfg &c, const Batch &b, const int32_t *idx, c
   // Stage 1 reads only the condensed q/k/v and writes o_imp and the
   // important rows of hidden; the hybrid KV (which stage 2 reads), stage 2
   // and the merge (question rows of hidden) touch none of that, so stage 1
-  // runs beside them on the second stream.
+  // runs beside them: in stage 2's launch, or on the second stream.
   if (one_launch(c, self, qdoc.attn)) {
     CHECK(fuse_impl(c, b, DAF_FUSE_KV, idx, k_imp, v_imp, k_q, v_q, k_cache, v_cache, nullptr, nullptr, nullptr,
                     stream));

@@ -1,5 +1,5 @@
 // Internal declarations shared by the DAF HIP kernels and the host library.
-// gfx950 (MI355X) only: wave64, MFMA bf16 32x32x16, 8 XCDs.
+// gfx950 (MI355X) only: wave64, MFMA bf16 16x16x32, 8 XCDs.
 #pragma once
 
 #include <hip/hip_runtime.h>
