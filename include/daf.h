@@ -49,10 +49,11 @@
  *   probabilities, so each output row is a weighted mean of value rows with
  *   weights that sum to one; its LSE is the log of that same sum, within
  *   ln(1 + 2^-8) of the exact log-sum-exp (the bf16 rounding of a term that
- *   dominates its row). The unnormalised fp32 sums hold probabilities below 2
- *   (scaled by a power of two per row), so value magnitudes times twice the
- *   key count must stay within fp32 (|V| below ~1e33
- *   for 32k keys). Stage 2's key splits keep their normalised partial outputs
+ *   dominates its row). The unnormalised fp32 sums hold probabilities of at most
+ *   2^32 per 16 keys (a row's running max is raised only past that), so value
+ *   magnitudes times 2^32 per 16 keys must stay within fp32 (|V| below ~1e26
+ *   for 32k keys); small values keep their precision down to bf16's smallest
+ *   normal ones. Stage 2's key splits keep their normalised partial outputs
  *   in the input dtype (bf16: one more rounding of each split's weighted mean
  *   before the log-sum-exp merge) and their LSE in fp32.
  * Asynchrony. Work is enqueued on `stream` (NULL = the default stream) and the

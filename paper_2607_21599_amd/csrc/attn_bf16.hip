@@ -21,11 +21,11 @@
 //    read from the row-major V tile with ds_read_b64_tr_b16, which transposes
 //    16-bit data across each 16-lane group.
 //  * Softmax in fp32, base 2, scale folded into one FMA per score, against a
-//    running reference per row that lies kHeadroom above the row's max, so no
-//    max is taken: the half tile's probabilities are formed and rounded, and
-//    their bits are ORed to see whether one has reached 2 (then the exact max
-//    is taken, the reference raised, O and the sum rescaled, the half formed
-//    again; always so on a row's first tile).
+//    running reference per row, so no max of the scores is taken: the half
+//    tile's probabilities are formed and rounded, and only if one of them has
+//    reached 2^28 (a packed maximum of their bits) is the exact max taken, the
+//    reference raised, O and the sum rescaled and the half formed again (always
+//    so on a row's first tile).
 //  * The row sum is one more MFMA per half tile and 16 rows, of the rounded
 //    probabilities against ones.
 //
@@ -62,13 +62,12 @@ typedef __attribute__((address_space(3))) bf16x4 lds_bf16x4;
 
 constexpr int kBN = 64;                  // keys per tile
 [[maybe_unused]] constexpr int kRsrcWord3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
-// Probabilities are formed against a running reference per row: the largest
-// scaled score at its last raise plus kHeadroom (log2 units), so they are at
-// most about 2^-32 until a later score exceeds that one. Only if one reaches 2
-// is the exact max taken, the reference raised and the probabilities formed
-// again: with every product below 2 V there is no overflow, and bf16's
-// exponent range keeps terms down to 2^-94 of the largest.
-constexpr float kHeadroom = 32.0f;
+// Probabilities are formed against a running reference per row, the largest
+// scaled score at its last raise: 1 there, so that products with values down to
+// the smallest normal ones stay normal in fp32. Only if a probability reaches
+// 2^28 (kLimit, its bf16 bits; at most 2^32 per 16 keys) is the exact max taken,
+// the reference raised and the probabilities formed again.
+constexpr unsigned kLimit = (127 + 28) << 7;
 constexpr float kNoReference = -3e38f;  // before the first key: every visible one's probability is infinite
 
 template <int D>
@@ -185,7 +184,7 @@ struct WaveState {
   using Gm = Geo<D>;
   bf16x8 qf[NB][Gm::DS];    // Q rows as the B operand of S^T
   f32x4 oacc[NB][Gm::DB];   // O^T accumulators
-  float m_run[NB];          // running max, scaled base-2 units, equal in a row's four lanes
+  float m_run[NB];          // running reference, scaled base-2 units, equal in a row's four lanes
   f32x4 lacc[NB];           // row sums of the rounded probabilities (four equal elements)
   int koff[Gm::DS];        // K tile read offsets
   int voff[Gm::DB];        // V tile transposed-read offsets
@@ -202,9 +201,19 @@ struct WaveState {
 template <int NB>
 using Scores = f32x4[2][NB];
 
+// The larger of three bf16 values, in both halves of a word: bits of values that
+// are not negative order alike as fp16, and a pattern of an fp16 NaN (2^121 and
+// more) stays one. Two of these per 16 rows and half tile; as four integer
+// maxima of two words they cost the 32k layer 1.6% and position_attn at 16k 4%.
+__device__ __forceinline__ unsigned max3_pairs(unsigned a, unsigned b, unsigned c) {
+  unsigned r;
+  asm("v_pk_maximum3_f16 %0, %1, %2, %3" : "=v"(r) : "v"(a), "v"(b), "v"(c));
+  return r;
+}
+
 // P^T operands (bf16) of one 32-key half, against the running reference m.
-// Returns the OR of their bits: bit 14 of either half is set if some
-// probability is 2 or more (the top exponent bit of a positive bf16).
+// Returns the largest of their bit patterns (which order like the values: none is
+// negative), over the even and over the odd ones.
 template <int D, int NB>
 __device__ __forceinline__ unsigned softmax_half(const WaveState<D, NB> &w, const Scores<NB> &sc, const float (&m)[NB],
                                                  bf16x8 (&pf)[NB]) {
@@ -213,16 +222,16 @@ __device__ __forceinline__ unsigned softmax_half(const WaveState<D, NB> &w, cons
 #pragma unroll
     for (int r = 0; r < 8; ++r)
       pf[nb][r] = (__bf16)fast_exp2(__builtin_fmaf(sc[r >> 2][nb][r & 3], w.sl2, -m[nb]));
-  unsigned bits = 0;
-#pragma unroll
-  for (int nb = 0; nb < NB; ++nb) {
-    const u32x4 a = __builtin_bit_cast(u32x4, pf[nb]);
-    bits |= (a[0] | a[1]) | (a[2] | a[3]);
+  const u32x4 a = __builtin_bit_cast(u32x4, pf[0]);
+  unsigned top = max3_pairs(max3_pairs(a[0], a[1], a[2]), a[3], a[3]);
+  if constexpr (NB == 2) {
+    const u32x4 b = __builtin_bit_cast(u32x4, pf[1]);
+    top = max3_pairs(max3_pairs(max3_pairs(max3_pairs(a[0], a[1], a[2]), a[3], b[0]), b[1], b[2]), b[3], b[3]);
   }
-  return bits;
+  return top;
 }
-__device__ __forceinline__ bool out_of_range(unsigned bits) {
-  return __builtin_amdgcn_ballot_w64((bits & 0x40004000u) != 0) != 0;
+__device__ __forceinline__ bool out_of_range(unsigned top) {
+  return __builtin_amdgcn_ballot_w64((top >> 16) >= kLimit || (top & 0xffffu) >= kLimit) != 0;
 }
 
 // O^T += V^T P^T over the 32 keys of one half tile. Contraction slot 8 g + j of
@@ -246,13 +255,13 @@ __device__ __forceinline__ void pv_half(WaveState<D, NB> &w, const bf16x8 (&a)[G
   for (int nb = 0; nb < NB; ++nb) w.lacc[nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones, pf[nb], w.lacc[nb], 0, 0, 0);
 }
 
-// Raise the running references to the rows' maxima mt plus the headroom,
-// rescaling O and the row sums.
+// Raise the running references to the rows' maxima mt, rescaling O and the row
+// sums.
 template <int D, int NB>
 __device__ __forceinline__ void raise_to(WaveState<D, NB> &w, const float (&mt)[NB]) {
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
-    const float m_new = fmaxf(w.m_run[nb], mt[nb] + kHeadroom);
+    const float m_new = fmaxf(w.m_run[nb], mt[nb]);
     const float alpha = fast_exp2(w.m_run[nb] - m_new);
     w.m_run[nb] = m_new;
     w.lacc[nb] *= alpha;
@@ -271,10 +280,10 @@ __device__ __forceinline__ void half_max(const WaveState<D, NB> &w, const Scores
   }
 }
 // Probabilities of a half tile: against the running reference as it stands,
-// and again after raising it if one of them is 2 or more.
+// and again after raising it if one of them is out of range.
 template <int D, int NB>
-__device__ __forceinline__ void finish_half(WaveState<D, NB> &w, const Scores<NB> &sc, bf16x8 (&pf)[NB], unsigned bits) {
-  if (out_of_range(bits)) {
+__device__ __forceinline__ void finish_half(WaveState<D, NB> &w, const Scores<NB> &sc, bf16x8 (&pf)[NB], unsigned top) {
+  if (out_of_range(top)) {
     float mt[NB];
     half_max<D, NB>(w, sc, mt);
     raise_to<D, NB>(w, mt);
@@ -310,7 +319,7 @@ __device__ __forceinline__ void tile_math(WaveState<D, NB> &w, const unsigned ch
 #pragma unroll
         for (int nb = 0; nb < NB; ++nb) s1[b][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[2 + b][ds], w.qf[nb][ds], s1[b][nb], 0, 0, 0);
     bf16x8 pf0[NB], pf1[NB];
-    const unsigned bits0 = softmax_half<D, NB>(w, s0, w.m_run, pf0);
+    const unsigned top0 = softmax_half<D, NB>(w, s0, w.m_run, pf0);
     // scheduling: K reads of half 0, the S MFMAs of half 0 in pairs beside a K
     // read of half 1, then the S MFMAs of half 1 in pairs beside a share of
     // the softmax of half 0
@@ -325,12 +334,12 @@ __device__ __forceinline__ void tile_math(WaveState<D, NB> &w, const unsigned ch
       __builtin_amdgcn_sched_group_barrier(0x008, NB, 0);
       __builtin_amdgcn_sched_group_barrier(0x002, 3 * NB, 0);
     }
-    finish_half<D, NB>(w, s0, pf0, bits0);
+    finish_half<D, NB>(w, s0, pf0, top0);
     bf16x8 v[Geo<D>::DB];
     read_v<D, NB>(w, vs, v);
     pv_half<D, NB>(w, v, pf0);
-    const unsigned bits1 = softmax_half<D, NB>(w, s1, w.m_run, pf1);
-    finish_half<D, NB>(w, s1, pf1, bits1);
+    const unsigned top1 = softmax_half<D, NB>(w, s1, w.m_run, pf1);
+    finish_half<D, NB>(w, s1, pf1, top1);
     read_v<D, NB>(w, vs + 32 * ROWB, v);
     pv_half<D, NB>(w, v, pf1);
     return;

@@ -1,0 +1,50 @@
+"""GPU: the value range and the LSE of the bf16 attention kernels, against the
+oracle. Probabilities are 1 at a row's reference score, so the fp32 sums
+represent values of any normal magnitude; include/daf.h states the upper bound."""
+from __future__ import annotations
+
+import numpy as np
+import pytest
+import torch
+
+import daf_inputs as di
+from parity import assert_attn_close, oracle_request
+
+pytestmark = pytest.mark.gpu
+
+
+def _layer(shape, arrays):
+    """Both stages by their own calls; the outputs as float64."""
+    from paper_2607_21599_amd.tensors import LayerBuffers
+    batch = di.make_batch([shape])
+    arrays(batch.arrays)
+    buf = LayerBuffers(batch.arrays, batch.cu_doc, batch.cu_q, batch.cu_imp, shape.hq, shape.hkv, shape.d)
+    buf.fuse_kv()
+    buf.stage1()
+    buf.stage2()
+    torch.cuda.synchronize()
+    out = {k: buf[k].float().cpu().numpy().astype(np.float64) for k in ("o_imp", "lse_imp", "o_q", "lse_q")}
+    return out, batch.request(0)
+
+
+@pytest.mark.parametrize("log2_scale,jump", [(-118, 20), (-100, 20), (84, 46)])
+@pytest.mark.parametrize("n,d,back", [(150, 128, 20), (300, 64, 33), (2200, 128, 33), (2200, 128, 20)])
+def test_values_of_any_magnitude(n, d, back, log2_scale, jump):
+    """Values of 2^-118 (outputs of 2^-124 are still normal) to 2^84, with a key
+    `jump` log2 units above the rest late in the sequence (64-row and 128-row
+    blocks; an even and an odd key): the outputs are as close as those of values
+    of order one. 2^46 times values of 2^84 would overflow: that key raises the
+    reference."""
+    def scale(a):
+        for k, rows in (("v_imp", n), ("v_q", 40), ("v_cache", n + 900)):
+            a[k][:rows] = di.f32_to_bf16_bits(di.raw_to_f32(a[k][:rows]) * np.float32(2.0 ** log2_scale))
+        u = np.full(d, 1.0 / np.sqrt(d), np.float32)
+        a["q_imp"] = di.f32_to_bf16_bits(di.raw_to_f32(a["q_imp"]) + np.float32(8.0) * u)
+        k = di.raw_to_f32(a["k_imp"])
+        k[n - back] = np.float32(jump * np.log(2.0) / 8.0 * np.sqrt(d)) * u
+        a["k_imp"] = di.f32_to_bf16_bits(k)
+    got, req = _layer(di.Shape("range", L_d=n + 900, L_q=40, n=n, hq=28, hkv=4, d=d, seed=n + d), scale)
+    rows = np.unique(np.r_[0:n:max(1, n // 40), n - 40:n])
+    ref = oracle_request(req, rows1=rows)
+    for name, g, r in (("stage 1", got["o_imp"][rows], ref["o_imp"]), ("stage 2", got["o_q"], ref["o_q"])):
+        assert_attn_close(g * 2.0 ** -log2_scale, r * 2.0 ** -log2_scale, di.BF16, f"{name}, values 2^{log2_scale}")
