@@ -48,3 +48,31 @@ def test_values_of_any_magnitude(n, d, back, log2_scale, jump):
     ref = oracle_request(req, rows1=rows)
     for name, g, r in (("stage 1", got["o_imp"][rows], ref["o_imp"]), ("stage 2", got["o_q"], ref["o_q"])):
         assert_attn_close(g * 2.0 ** -log2_scale, r * 2.0 ** -log2_scale, di.BF16, f"{name}, values 2^{log2_scale}")
+
+
+@pytest.mark.parametrize("n,L_d,loud", [(64, 300, 40), (128, 300, 100), (2200, 2300, 2180), (64, 100, 0)])
+def test_lse_of_a_dominating_key_in_a_masked_tile(n, L_d, loud):
+    """One key 18.49 log2 units above all others (scores of 0), first met in a
+    row's masked tile: in stage 1 at `loud`, in stage 2 (loud 0) question token
+    10. 2^0.49 is not a bf16 number, so the key's probability is exact only
+    against its own score. What is left are the others' roundings, 2^-9 of at
+    most 2200 x 2^-18.49, and fp32's: the bar is 1e-4 (a rounding of the key's
+    own probability is 1e-3)."""
+    d = 128
+
+    def arrays(a):
+        q = np.zeros(d, np.float32)
+        q[0] = 8.0
+        for k in ("q_imp", "q_q"):
+            a[k][:] = di.f32_to_bf16_bits(q)
+        for k in ("k_imp", "k_q", "k_cache"):
+            a[k][:] = 0
+        key = np.zeros(d, np.float32)
+        key[0] = 18.125
+        (a["k_imp"] if loud else a["k_q"])[loud or 10] = di.f32_to_bf16_bits(key)
+    got, req = _layer(di.Shape("lse", L_d=L_d, L_q=20, n=n, hq=28, hkv=4, d=d, seed=n + loud), arrays)
+    rows = np.arange(loud, n) if loud else np.arange(1)
+    ref = oracle_request(req, rows1=rows)
+    g, r = (got["lse_imp"].T[rows], ref["lse_imp"]) if loud else (got["lse_q"].T[10:], ref["lse_q"][10:])
+    err = np.abs(g - r).max()
+    assert err <= 1e-4, err
