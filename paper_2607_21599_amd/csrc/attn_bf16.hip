@@ -232,7 +232,7 @@ __device__ __forceinline__ unsigned softmax_half(const WaveState<D, NB> &w, cons
   return top;
 }
 __device__ __forceinline__ bool out_of_range(unsigned top) {
-  return __builtin_amdgcn_ballot_w64((top >> 16) >= kLimit || (top & 0xffffu) >= kLimit) != 0;
+  return __builtin_amdgcn_ballot_w64(top >= kLimit << 16 || (unsigned short)top >= kLimit) != 0;
 }
 
 // O^T += V^T P^T over the 32 keys of one half tile. Contraction slot 8 g + j of
@@ -367,17 +367,19 @@ __device__ __forceinline__ void tile_math(WaveState<D, NB> &w, const unsigned ch
         for (int nb = 0; nb < NB; ++nb)
           sc[h][b][nb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(kf[b][ds], w.qf[nb][ds], sc[h][b][nb], 0, 0, 0);
   }
+  if (kb + kBN - 1 > w.wave_first_limit) {  // not so in most first tiles
 #pragma unroll
-  for (int h = 0; h < 2; ++h)
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < 2; ++b)
 #pragma unroll
-      for (int nb = 0; nb < NB; ++nb)
+        for (int nb = 0; nb < NB; ++nb)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const int key = kb + 32 * h + 16 * b + 4 * w.quad + e;
-          if (key > w.limit[nb]) sc[h][b][nb][e] = -INFINITY;
-        }
+          for (int e = 0; e < 4; ++e) {
+            const int key = kb + 32 * h + 16 * b + 4 * w.quad + e;
+            if (key > w.limit[nb]) sc[h][b][nb][e] = -INFINITY;
+          }
+  }
   // The max of the whole tile, and the reference raised past a growth of
   // kMaskedSlack: a key that dominates its row from here on has a probability of
   // 1, which bf16 holds exactly, so that its weight in the row's sum is exact
