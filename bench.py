@@ -49,7 +49,7 @@ EVICT_MIB = 512  # scratch streamed through before each timed stage call (MALL i
 # build the work tables, plan the key splits and launch the merge. A profile
 # record taken on other versions of these is not used.
 ATTN_SOURCES = [os.path.join(ROOT, "paper_2607_21599_amd", "csrc", f)
-                for f in ("attn_bf16.hip", "attn.hip", "daf_internal.h")] + [
+                for f in ("attn_bf16.hip", "attn.hip", "block_rule.h", "daf_internal.h")] + [
     os.path.join(ROOT, "paper_2607_21599_amd", "build.py")]
 ATTN_HOST = os.path.join(ROOT, "paper_2607_21599_amd", "csrc", "api.hip")
 ATTN_HOST_FUNCTIONS = ("AttnEntry self_entry(", "int entry_groups(", "daf_status_t run_entries(",

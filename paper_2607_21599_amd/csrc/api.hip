@@ -356,14 +356,16 @@ daf_status_t run_entries(const Cfg &c, AttnKind kind, const std::vector<AttnEntr
 // (two events and two waits, about 20 us of host time and 6 + 5 us between
 // kernels), and the jobs of one stage fill in where the other's leave CUs idle:
 // 16k keys, n = 2458: 120 us on two streams, 105 in one launch; 32k, n = 4915
-// 261 and 251; eight requests 872 and 869. The fp32 kernel takes its small
-// layers so.
+// 261 and 251; eight requests 872 and 869. The fp32 kernel takes layers of up to
+// kF32OneLaunchJobs so (28 heads of 128, n = 154 / 615 / 2000, two streams and one
+// launch: 81 / 224 / 642 us and 47 / 151 / 487; 4 heads of 64, n = 600: 85 and 71).
+constexpr int64_t kF32OneLaunchJobs = 448;
 bool one_launch(const Cfg &c, const std::vector<AttnEntry> &self, const std::vector<AttnEntry> &qdoc) {
   if (self.empty() || qdoc.empty() || self.size() + qdoc.size() > (size_t)kMaxEntries) return false;
   if (c.dtype == DAF_BF16) return true;
   int64_t jobs = 0;
   for (const AttnEntry &e : self) jobs += (int64_t)e.mb_count * c.hq;
-  return jobs <= kNarrowJobs;
+  return jobs <= kF32OneLaunchJobs;
 }
 
 daf_status_t run_both(const Cfg &c, const std::vector<AttnEntry> &self, const std::vector<AttnEntry> &qdoc,

@@ -649,6 +649,27 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_both_kernel(const AttnLa
   else attn_job<D, 1, 2>(p, p.list[1], xcd, u - n1, k_lds0, v_lds0, k_lds1, v_lds1);
 }
 
+// Rows at given positions where the positions decide the block height: one job
+// per workgroup, list[0] (e[0]) in 64-row and list[1] (e[1], the same rows) in
+// 128-row blocks; the grid holds the former. The positions ascend, so the middle
+// one over the last estimates the chains' mean share of the longest. 28 heads of
+// 128, 32768 keys, always 64 rows and now: 1792 rows spread over the keys 512 and
+// 521 us, at their end 1059 and 861.
+template <int D>
+__global__ __launch_bounds__(kAttnThreads, 2) void attn_positions_kernel(const AttnLaunch p) {
+  constexpr int TILE = Geo<D>::TILE;
+  __shared__ __attribute__((aligned(1024))) unsigned char k_lds0[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_lds0[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char k_lds1[TILE];
+  __shared__ __attribute__((aligned(1024))) unsigned char v_lds1[TILE];
+  const int xcd = blockIdx.x % kXcds, u = blockIdx.x / kXcds;
+  const AttnEntry &E = p.e[0];
+  const double share = (double)E.q_pos[E.n_rows / 2] / (E.q_pos[E.n_rows - 1] + 1);
+  const bool narrow = narrow_pays(D, (long long)p.list[1].n_groups * p.group, share);
+  if (narrow) attn_job<D, 0, 1>(p, p.list[0], xcd, u, k_lds0, v_lds0, k_lds1, v_lds1);
+  else if (u < p.list[1].slots_per_xcd) attn_job<D, 0, 2>(p, p.list[1], xcd, u, k_lds0, v_lds0, k_lds1, v_lds1);
+}
+
 // Slots per XCD of a list: work groups per XCD times the workgroups of one.
 int list_slots(const AttnLaunch &p, const AttnList &l) {
   int per_xcd;
@@ -673,18 +694,45 @@ void narrow_blocks(AttnLaunch &p, AttnList &l) {
   }
 }
 
+// The rule's share of a list (all rows without given positions).
+double chain_share(const AttnLaunch &p, const AttnList &l) {
+  double work = 0, blocks = 0, longest = 1;
+  for (int i = l.e0; i < l.e0 + l.n_entries; ++i) {
+    const AttnEntry &e = p.e[i];
+    work += e.mb_count * (e.n_keys - 0.5 * e.n_rows);
+    blocks += e.mb_count;
+    longest = std::max(longest, (double)e.n_keys);
+  }
+  return blocks > 0 ? work / (blocks * longest) : 0.0;
+}
+
+template <int D>
+hipError_t launch_positions_t(const AttnLaunch &p0, hipStream_t st) {
+  AttnLaunch p = p0;
+  p.list[1] = p.list[0];
+  p.list[1].e0 = 1;
+  p.e[1] = p.e[0];
+  narrow_blocks(p, p.list[0]);
+  for (AttnList &l : p.list) l.slots_per_xcd = list_slots(p, l);
+  attn_positions_kernel<D><<<dim3(kXcds * p.list[0].slots_per_xcd), dim3(kAttnThreads), 0, st>>>(p);
+  return hipGetLastError();
+}
+
 template <int D>
 hipError_t launch_t(AttnKind kind, const AttnLaunch &p0, hipStream_t st) {
   AttnLaunch p = p0;
   AttnList &l = p.list[0];
-  // Causal self attention of at most kNarrowJobs 128-row blocks (times heads)
-  // runs 64-row blocks, 16 rows per wave: twice the workgroups, and the longest
-  // block's chain of key tiles, which is what such a launch takes, is shorter
-  // per tile. n = 512 / 922 / 1500 of 28 heads (112 / 224 / 336 blocks): 14.6 /
-  // 21.6 / 33.5 us with 128 rows, 10.7 / 17.0 / 27.3 with 64; n = 2000 (448)
-  // 43.2 and 42.7, n = 2458 (560) 54.7 and 57.4: above, the slots are full and
-  // the doubled K/V copies per row cost more.
-  const bool narrow = kind == AttnKind::kSelf && l.n_groups * p.group <= kNarrowJobs;
+  // 64-row blocks (16 rows per wave) where the rule says so. Stage 1, n = 512 /
+  // 922 / 1500 of 28 heads (112 / 224 / 336 jobs): 14.6 / 21.6 / 33.5 us with 128
+  // rows, 10.7 / 17.0 / 27.3 with 64; n = 2000 (448) 43.2 and 42.7, n = 2458 (560)
+  // 54.7 and 57.4.
+  const long long jobs = (long long)l.n_groups * p.group;
+  bool narrow = false;
+  if (kind == AttnKind::kSelf) {
+    const bool given = p.e[0].q_pos != nullptr;  // one entry
+    if (given && jobs > narrow_always(D) && jobs <= narrow_most(D)) return launch_positions_t<D>(p, st);
+    narrow = narrow_pays(D, jobs, given ? 1.0 : chain_share(p, l));
+  }
   if (narrow) narrow_blocks(p, l);
   const int slots = list_slots(p, l);
   // Causal self attention: the heaviest 2 * kResidentPerXcd slots of an XCD
@@ -714,7 +762,7 @@ template <int D>
 hipError_t launch_both_t(const AttnLaunch &p0, hipStream_t st) {
   AttnLaunch p = p0;
   AttnList &l1 = p.list[0], &l2 = p.list[1];
-  const bool narrow = l1.n_groups * p.group <= kNarrowJobs;
+  const bool narrow = narrow_pays(D, (long long)l1.n_groups * p.group, chain_share(p, l1));
   if (narrow) narrow_blocks(p, l1);
   for (AttnList &l : p.list) l.slots_per_xcd = list_slots(p, l);
   // Which stage's jobs go first, from an estimate of the time in key tiles of a

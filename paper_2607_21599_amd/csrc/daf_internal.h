@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "block_rule.h"
+
 namespace daf {
 
 constexpr int kXcds = 8;          // MI355X: 8 XCDs, workgroups dispatched round-robin
@@ -72,7 +74,9 @@ struct AttnList {
 struct AttnLaunch {
   int32_t hq, hkv, group;  // group = Hq / Hkv
   float scale_log2;        // softmax scale * log2(e)
-  AttnList list[2];        // list[1]: stage 2 beside stage 1 in one launch (bf16), else unused
+  // list[1] (bf16): stage 2 beside stage 1 in one launch, or the same rows in
+  // 128-row blocks where the kernel picks the block height; else unused
+  AttnList list[2];
   AttnEntry e[kMaxEntries];
 };
 static_assert(sizeof(AttnLaunch) < 4096, "attention launch table must fit 4 KiB of kernel arguments");
@@ -155,9 +159,6 @@ hipError_t launch_attention_bf16(int head_dim, AttnKind kind, const AttnLaunch &
                                  hipStream_t s);
 // Stage 1 (list[0]) and stage 2 (list[1]) in one launch (bf16).
 hipError_t launch_attention_both_bf16(int head_dim, const AttnLaunch &p, hipStream_t s);
-// Causal self attention of at most this many 128-row blocks times heads runs
-// 64-row blocks (attn_bf16.hip).
-constexpr int kNarrowJobs = 448;
 hipError_t launch_merge(int dtype, int head_dim, const MergeLaunch &p,
                         hipStream_t s);
 // merge of the bf16 stage-2 split partials (attn_bf16.hip)
