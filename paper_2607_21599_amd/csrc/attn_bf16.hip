@@ -29,16 +29,20 @@
 //  * The row sum is one more MFMA per half tile and 16 rows, of the rounded
 //    probabilities against ones.
 //
-// What bounds it: the VALU issue port, which the softmax and the MFMAs share
-// (an MFMA of either shape holds it for about 8 cycles, v_exp_f32 and
-// v_cvt_pk_bf16_f32 for about 8, other VALU operations for 4.4), and the clock,
-// which the chip's power sets. Beside a wave that issues MFMAs back to back a
-// v_dot2 waits about 50 cycles, so the previous row sum (16 v_dot2 per tile
-// and wave) cost more than the 4 MFMAs that replaced it, and the 16x16x32
-// shape needs less power per FLOP than 32x32x16. Stage 1 at n = 4915, 28 heads
-// of 128: 173 us with 32x32x16 MFMAs and v_dot2, 166 with 16x16x32, 163 with
-// the sum on the matrix cores; 5043 rows at positions of 32896 keys: 1122, 1062
-// and 1045 us.
+// What bounds it: how far a wave's phases (S from K fragments, softmax, P V from
+// V fragments) overlap with those of the one other wave of its SIMD (two fit: 256
+// VGPRs and 64 KiB of LDS per workgroup), and the clock, which the chip's power
+// sets. Stage 1 at n = 4915, 28 heads of 128 (profiles of the standalone call): the
+// matrix cores are busy 47% of the cycles and VALU issue 41%; the 32 KiB of
+// fragments per tile and wave need 48% of the LDS's 128 bytes per cycle. Copies of
+// the kernel with one part taken out (163 us whole): 143 us without the softmax,
+// 122 without the fragments' LDS reads, 105 without both, 148 without the copies
+// to LDS; the matrix work alone is 83 us at that clock.
+//   16x16x32 MFMAs need less power per FLOP than 32x32x16, and beside a wave that
+// issues MFMAs back to back a v_dot2 waits about 50 cycles, so 4 MFMAs per tile
+// took the place of 16 v_dot2 for the row sums: 173 us with 32x32x16 MFMAs and
+// v_dot2, 166 with 16x16x32, 163 with the sum on the matrix cores; 5043 rows at
+// positions of 32896 keys: 1122, 1062 and 1045 us.
 //
 // Launch shape for causal self attention: the heaviest 128 jobs of an XCD (one
 // query head of one 128-row block each) are run by its 64 resident workgroups
@@ -653,8 +657,8 @@ __global__ __launch_bounds__(kAttnThreads, 2) void attn_both_kernel(const AttnLa
 // per workgroup, list[0] (e[0]) in 64-row and list[1] (e[1], the same rows) in
 // 128-row blocks; the grid holds the former. The positions ascend, so the middle
 // one over the last estimates the chains' mean share of the longest. 28 heads of
-// 128, 32768 keys, always 64 rows and now: 1792 rows spread over the keys 512 and
-// 521 us, at their end 1059 and 861.
+// 128, 32768 keys, always 64 rows and now: 1792 rows spread over the keys 481 and
+// 491 us, at their end 1039 and 795.
 template <int D>
 __global__ __launch_bounds__(kAttnThreads, 2) void attn_positions_kernel(const AttnLaunch p) {
   constexpr int TILE = Geo<D>::TILE;
