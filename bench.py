@@ -52,7 +52,8 @@ ATTN_SOURCES = [os.path.join(ROOT, "paper_2607_21599_amd", "csrc", f)
                 for f in ("attn_bf16.hip", "attn.hip", "block_rule.h", "daf_internal.h")] + [
     os.path.join(ROOT, "paper_2607_21599_amd", "build.py")]
 ATTN_HOST = os.path.join(ROOT, "paper_2607_21599_amd", "csrc", "api.hip")
-ATTN_HOST_FUNCTIONS = ("AttnEntry self_entry(", "int entry_groups(", "daf_status_t run_entries(",
+ATTN_HOST_FUNCTIONS = ("AttnEntry self_entry(", "int entry_groups(", "AttnLaunch new_launch(", "void add_list(",
+                       "daf_status_t run_entries(",
                        "void add_self_entries(", "bool packed_qdoc(", "int qdoc_blocks(",
                        "std::vector<Split> plan_splits(", "WsLayout ws_layout(", "AttnEntry qdoc_entry(",
                        "daf_status_t qdoc_entries(", "daf_status_t run_merge(")
@@ -61,11 +62,8 @@ ATTN_HOST_FUNCTIONS = ("AttnEntry self_entry(", "int entry_groups(", "daf_status
 def _function_text(src: str, head: str) -> str:
     """The text of the function that starts with `head` up to its closing
     brace at the start of a line."""
-    i = src.find(head)
-    if i < 0:
-        return ""
-    j = src.find("\n}\n", i)
-    return src[i:j + 3]
+    i = src.index("\n" + head) + 1  # a function that is gone or renamed is an error
+    return src[i:src.index("\n}\n", i) + 3]
 
 
 def attn_source_hash() -> str:

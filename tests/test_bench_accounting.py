@@ -86,3 +86,21 @@ def test_committed_profiles_match_the_sources():
         assert bench.record_number(trace, key) is not None, key
     for key in ("stage1_hbm_bytes_per_launch", "stage2_hbm_bytes_per_launch", "merge_hbm_bytes_per_launch"):
         assert bench.record_number(traffic, key) is not None, key
+
+
+@pytest.mark.parametrize("text", ["p.scale_log2 = c.scale", "e.group0 = l.n_groups", "l.wgs_per_group = ",
+                                  "e.n_splits = 1", "per_wg = work / kTargetWorkgroups", "p.total_rows = rows"])
+def test_source_hash_covers_the_table_construction(text, tmp_path, monkeypatch):
+    """A change to any host function that shapes a standalone stage launch makes
+    recorded profiles stale, and a listed function that is gone is an error."""
+    with open(bench.ATTN_HOST) as fh:
+        src = fh.read()
+    assert text in src
+    before = bench.attn_source_hash()
+    changed = tmp_path / "api.hip"
+    changed.write_text(src.replace(text, text + " 1 + "))
+    monkeypatch.setattr(bench, "ATTN_HOST", str(changed))
+    assert bench.attn_source_hash() != before
+    changed.write_text(src.replace("AttnLaunch new_launch(", "AttnLaunch fresh_launch("))
+    with pytest.raises(ValueError):
+        bench.attn_source_hash()
