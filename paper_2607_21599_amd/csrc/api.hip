@@ -166,9 +166,9 @@ std::vector<Split> plan_splits(const Cfg &c, const Batch &b) {
   }
   // key tiles per workgroup for two workgroups per CU; where that is few, one
   // per CU: a workgroup's fixed cost (about 5 us), its partial rows and the
-  // merge then weigh more than the longer chain (3 tiles, 6k keys and 64 rows:
-  // the call 21.1 us with two per CU, 19.2 with one; 8 tiles, 32k keys and 32
-  // rows: 30.1 and 30.0; 14 tiles, 16k keys and 128 rows: 4-8 us slower with one).
+  // merge then weigh more than the longer chain. Times with one over those with
+  // two, 28, 14 and 8 heads, questions of 8 to 200 rows: 0.80-0.94 at 2 to 3 tiles,
+  // 0.86-0.97 at 3 to 4, 0.85-1.00 at 4 to 4.9; at 14 tiles one is 4-8 us slower.
   // The fp32 kernel's tiles take several times as long, so it keeps two.
   double per_wg = work / kTargetWorkgroups;
   if (packed_qdoc(c) && per_wg < 5.0) per_wg *= 2.0;
