@@ -117,17 +117,18 @@ __global__ __launch_bounds__(kScoreThreads) void select_score_kernel(const Selec
 constexpr int kSlabKeys = kTopnThreads * 32;
 
 // Exclusive prefix sum over the waves of a wave-uniform value, in wave order;
-// also returns the sum over all waves. wsum: kTopnWaves ints of LDS.
-__device__ __forceinline__ int wave_scan(int v, int *wsum, int &total) {
+// also returns the sum over all waves. Unsigned: packed counts reach 2^31. wsum:
+// kTopnWaves words of LDS.
+__device__ __forceinline__ unsigned wave_scan(unsigned v, unsigned *wsum, unsigned &total) {
   const int wave = threadIdx.x >> 6;
   if ((threadIdx.x & 63) == 0) wsum[wave] = v;
   __syncthreads();
-  int before = 0;
+  unsigned before = 0;
   total = 0;
 #pragma unroll
   for (int w = 0; w < kTopnWaves; ++w) {
-    const int t = wsum[w];
-    before += w < wave ? t : 0;
+    const unsigned t = wsum[w];
+    before += w < wave ? t : 0u;
     total += t;
   }
   __syncthreads();  // wsum is reused by the next call
@@ -135,7 +136,7 @@ __device__ __forceinline__ int wave_scan(int v, int *wsum, int &total) {
 }
 
 // Exclusive prefix sum of v over the threads in thread order.
-__device__ __forceinline__ int block_scan(int v, int *wsum) {
+__device__ __forceinline__ int block_scan(int v, unsigned *wsum) {
   const int lane = threadIdx.x & 63;
   int inc = v;
 #pragma unroll
@@ -143,9 +144,8 @@ __device__ __forceinline__ int block_scan(int v, int *wsum) {
     const int t = __shfl_up(inc, off, 64);
     if (lane >= off) inc += t;
   }
-  int total;
-  const int before = wave_scan(__shfl(inc, 63, 64), wsum, total);
-  return before + inc - v;
+  unsigned total;
+  return (int)wave_scan((unsigned)__shfl(inc, 63, 64), wsum, total) + inc - v;
 }
 
 // Number of set bits of m below this lane.
@@ -160,7 +160,7 @@ __device__ __forceinline__ int uniform(int x) { return __builtin_amdgcn_readfirs
 __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectLaunch p) {
   __shared__ unsigned s_key[kSlabKeys + (kChunk - 1) * 64];
   __shared__ int hist[kHistCopies * kHistStride];
-  __shared__ int wsum[kTopnWaves];
+  __shared__ unsigned wsum[kTopnWaves];
   __shared__ unsigned s_lo[kTopnWaves], s_hi[kTopnWaves], s_base;
   __shared__ int s_remaining, s_top;
   const int b = blockIdx.x;
@@ -282,8 +282,8 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
       n_eq += __popcll(ballot(token) & ballot(k == T));
     });
     // both counts of a slab are at most 2^15: one scan takes them side by side
-    int totals;
-    const unsigned before = (unsigned)wave_scan((int)((unsigned)n_gt << 16 | (unsigned)n_eq), wsum, totals);
+    unsigned totals;
+    const unsigned before = wave_scan((unsigned)n_gt << 16 | (unsigned)n_eq, wsum, totals);
     const int eq_before = uniform((int)(before & 0xffffu));
     const int eq_keep = max(0, min(n_eq, remaining - eq_before));
     int pos = out_base + uniform((int)(before >> 16)) + min(eq_before, remaining);
@@ -310,8 +310,8 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
         pos += __popcll(km);
       });
     }
-    const int eq_total = uniform((int)((unsigned)totals & 0xffffu));
-    out_base += uniform((int)((unsigned)totals >> 16)) + min(eq_total, remaining);
+    const int eq_total = uniform((int)(totals & 0xffffu));
+    out_base += uniform((int)(totals >> 16)) + min(eq_total, remaining);
     remaining -= min(eq_total, remaining);
   }
 }
