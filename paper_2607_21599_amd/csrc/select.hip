@@ -26,11 +26,12 @@
 //   One CU does a request's work and runs each part of the code once or a few
 // times, so it is bound by latencies: of memory (a request's 128 KiB take about
 // 4 us to reach the CU), of the LDS behind each key, and of the instructions
-// themselves, which is why the loops are rolled. Score and top-n together, us,
-// with the keys in registers and straight code before: 1024 tokens 18.3, now
-// 11.4; 8192 26.7 and 18.4; 32768 56.4 and 53.8; 131072 (one layer) 124 and 116;
-// four requests of 3000 to 32768 37.5 and 36.2. Ranking the last 512 keys against
-// each other instead of the last passes cost 4 us more than the passes at 32768.
+// themselves, which is why the loops are rolled. Score and top-n together, us back
+// to back, 3 layers of 512 values per token, with the keys in registers and
+// straight code before: 1024 tokens 20.0, now 12.7; 8192 27.4 and 19.0; 32768 49.7
+// and 47.3; 33000 61.8 and 58.7 (70.8 with uneven slabs, each reloaded by every
+// pass); 131072 216 and 206, of one layer 111 and 110 (115). Ranking the last 512
+// keys against each other instead of the last passes cost 4 us more at 32768.
 #include "daf_internal.h"
 
 namespace daf {
@@ -113,7 +114,7 @@ __global__ __launch_bounds__(kScoreThreads) void select_score_kernel(const Selec
   if (lane == 0) p.scores[row] = acc / (float)p.n_layers;
 }
 
-// Keys in LDS at a time (128 KiB); a longer request is reloaded per pass.
+// Most keys in LDS at a time (128 KiB); a longer request is reloaded per pass.
 constexpr int kSlabKeys = kTopnThreads * 32;
 
 // Exclusive prefix sum over the waves of a wave-uniform value, in wave order;
@@ -169,16 +170,21 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
   const unsigned *key = reinterpret_cast<const unsigned *>(p.scores + p.req[b].doc0);
   int32_t *out = p.idx + p.req[b].imp0;
   const int lane = threadIdx.x & 63, wave = uniform((int)(threadIdx.x >> 6));
-  const int n_slabs = (L - 1) / kSlabKeys + 1;
 
-  // a slab's keys are dealt to the waves in ranges of `steps` * 64, the same in
-  // every slab: a wave copies and reads its own range only, so the passes need no
-  // barrier around a slab
-  const int steps = (min(L, kSlabKeys) + kTopnThreads - 1) / kTopnThreads, own = wave * steps * 64;
-  int slab0 = 0, len = 0;  // first key and keys of the loaded slab
+  // slabs of equal size (33000 keys as 32768 + 232 took every pass the work of
+  // 65536), dealt to the waves in ranges of `steps` * 64, the same in every slab: a
+  // wave copies and reads its own range only, so the passes need no barrier around
+  // a slab. Passes go over the slabs in turns up and down, so that a pass begins
+  // with the slab that the one before ended with.
+  const int most = (L - 1) / kSlabKeys + 1, steps = ((L - 1) / most + kTopnThreads) / kTopnThreads;
+  const int slab = steps * kTopnThreads, n_slabs = (L - 1) / slab + 1, own = wave * steps * 64;
+  int loaded = -1, slab0 = 0, len = 0;  // the loaded slab, its first key and its keys
   auto load = [&](int s) {
-    slab0 = s * kSlabKeys;
-    len = min(L - slab0, kSlabKeys);
+    if (s == loaded) return;
+    loaded = s;
+    slab0 = s * slab;
+    len = min(L - slab0, slab);
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // every read of the slab before is done
     for (int j = 0; j < steps; ++j) {
       // lanes past the last key copy it again; every use below tests the index
       const unsigned *from = key + slab0 + min(own + j * 64 + lane, len - 1);
@@ -186,6 +192,14 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
                                        (__attribute__((address_space(3))) void *)&s_key[own + j * 64], 4, 0, 0);
     }
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+  };
+  bool down = false;
+  auto slabs = [&](auto f) {
+    for (int t = 0; t < n_slabs; ++t) {
+      load(down ? n_slabs - 1 - t : t);
+      f();
+    }
+    down = !down;
   };
   // f(key, its index in the wave's range, whether it is a token), in order. The
   // reads of a chunk are issued together: behind f's LDS atomics and stores each
@@ -205,13 +219,12 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
   // ---- the keys' range -------------------------------------------------------
   for (int i = threadIdx.x; i < kHistCopies * kHistStride; i += kTopnThreads) hist[i] = 0;
   unsigned lo = 0xffffffffu, hi = 0u;
-  for (int s = 0; s < n_slabs; ++s) {
-    load(s);
+  slabs([&] {
     each([&](unsigned k, int, bool token) {
       lo = min(lo, token ? k : 0xffffffffu);
       hi = max(hi, token ? k : 0u);
     });
-  }
+  });
 #pragma unroll
   for (int off = 32; off > 0; off >>= 1) {
     lo = min(lo, (unsigned)__shfl_xor((int)lo, off, 64));
@@ -239,13 +252,12 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
     const int w = min(8, top), shift = top - w;
     const unsigned last = ~0u >> (32 - top);
     int *mine = &hist[(lane & (kHistCopies - 1)) * kHistStride];
-    for (int s = 0; s < n_slabs; ++s) {
-      if (n_slabs > 1) load(s);
+    slabs([&] {
       each([&](unsigned k, int, bool token) {
         const unsigned r = k - base;
         if (token & (r <= last)) atomicAdd(&mine[r >> shift], 1);
       });
-    }
+    });
     __syncthreads();
     // digits from the highest down: the selected one holds the remaining-th key
     if (threadIdx.x == 0) s_top = 0;  // every pass ends the loop unless a digit is chosen
@@ -275,7 +287,7 @@ __global__ __launch_bounds__(kTopnThreads) void select_topn_kernel(const SelectL
   // ---- ordered compaction, slab by slab ----------------------------------------
   int out_base = 0;  // kept keys of earlier slabs
   for (int s = 0; s < n_slabs; ++s) {
-    if (n_slabs > 1) load(s);
+    load(s);
     int n_gt = 0, n_eq = 0;
     each([&](unsigned k, int, bool token) {
       n_gt += __popcll(ballot(token) & ballot(k > T));
