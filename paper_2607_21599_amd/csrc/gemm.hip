@@ -113,7 +113,7 @@ __device__ __forceinline__ void issue(const Copy &c, const uint32_t (&voff)[2]) 
       "buffer_load_dwordx4 %3, %4, 0 offen lds"
       :
       : "s"(c.lds), "s"(c.lds + 1024), "v"(voff[0]), "v"(voff[1]), "s"(c.r)
-      : "memory");
+      : "memory", "m0");
 #endif
 }
 
