@@ -19,7 +19,7 @@
 // Both operands are K-contiguous, as the matrix cores take them. All of the LDS
 // is a ring of ten 16 KiB regions of 128 rows x 128 bytes (A rows half 0 / half
 // 1, W columns 0-31 / 32-63 of every wave), 16-byte chunks XOR-swizzled by
-// (row / 2) mod 8: no bank conflicts (SQ_LDS_BANK_CONFLICT = 0). Regions pass
+// (row / 2) mod 8: no bank conflicts in the loop. Regions pass
 // through it in the order in which they are read. A slot is copied into again
 // two phases after its fragments were read (by then both groups have read it),
 // eight phases before its new region is, and that copy is waited for with a
@@ -27,20 +27,21 @@
 // barriers. (Two k steps of regions and copies six phases ahead: 5-6% slower in
 // a decoder layer, where the weights come from HBM.)
 //
-// What bounds it: the chip's power. At 8192^3 the matrix cores are busy 83% of
-// the cycles, but at a shader clock of 1.5-1.6 GHz; the instruction that needs
-// less power per FLOP runs faster. v_mfma_f32_16x16x32_bf16 reads and writes
-// half the accumulator registers per FLOP of v_mfma_f32_32x32x16_bf16: an early
-// form of this kernel ran 868 us with 32x32x16 and 732 us with 16x16x32 (1502
-// TFLOP/s; the previous two-stage kernel with 32x32x16 ~1150). 64-byte rows per
-// copy (k steps of 32, four stages) doubled the L2 requests: 911 us. With few
-// rows it is HBM latency: 986 x 3584 x 18944 takes 168 us with the weights in
-// the caches and 231 us from HBM.
+// What bounds it: the chip's power, then the barriers between phases. At 8192^3
+// the matrix cores are busy 84% of the cycles, and the shader clock settles at
+// 1.75 GHz of 2.4: 727 us, 1512 TFLOP/s. The instruction that needs less power per
+// FLOP runs faster: v_mfma_f32_16x16x32_bf16 reads and writes half the accumulator
+// registers per FLOP of v_mfma_f32_32x32x16_bf16 (an early form of this kernel 868
+// us with the latter and 732 with the former; the previous two-stage kernel with
+// 32x32x16 ~1150 TFLOP/s). 64-byte rows per copy (k steps of 32, four stages)
+// doubled the L2 requests: 911 us. With few rows it is HBM latency: 986 x 3584 x
+// 18944 without a workspace takes 177 us with the weights in the caches and 231
+// from HBM; in the decoder layer, in two k pieces per half, 139 and 10 for the sum.
 //
 // Work list (plan_job): whole rounds of 256 tiles, one per CU, then the rest:
 // row ranges of at most 128 rows and, where that shortens the last round,
-// tiles of the last round cut in two 128 x 256 tiles (two phases per k step,
-// three LDS stages) and, given a workspace, cut along k, all in the same
+// tiles of the last round cut in two 128 x 256 tiles (two phases per k step, copies
+// seven and eight regions ahead) and, given a workspace, cut along k, all in the same
 // launch after the whole tiles.
 #include <algorithm>
 #include <type_traits>
