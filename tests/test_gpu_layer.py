@@ -143,9 +143,10 @@ def _layer_close(got, ref, what):
 def test_decoder_layer_daf(model, L_d, L_q, n):
     """One DAF layer: only the important and question rows are recomputed;
     the hybrid cache receives their roped K/V; the output is the compact
-    state (x of those rows after the layer). At the Qwen2.5-7B widths the
-    projections cut their tail tiles along k (986 rows: every tile, in pieces;
-    2586 rows: 512 whole tiles, then 76 in 6 pieces each, then the sum)."""
+    state (x of those rows after the layer). At the Qwen2.5-7B widths and 986
+    rows the output and down projections run as halves in 2 pieces along k, then
+    the sum, and the gated one as 512 whole tiles and 80 cut in halves; 2586 rows
+    are whole tiles and 26 last rows (test_gemm_plan.py)."""
     import paper_2607_21599_amd as daf
     from oracle import get as oracle_get
     x, kc, vc, idx, wts = _layer_setup(model, L_d, L_q, n, seed=L_d + n)
@@ -193,11 +194,10 @@ def test_decoder_layer_full():
 
 
 def test_decoder_layer_full_large_tiles_sampled():
-    """Full recomputation at the Qwen2.5-7B widths with 9300 rows: q_proj,
-    o_proj and the down projection take the 256 x 256 tile (518 tiles: two
-    whole rounds of 256, then 6 tail tiles cut along k, then the sum). The
-    oracle computes K/V for every row and the rest of the layer on sampled
-    rows, including rows of the tail tiles (M-tiles 32-36)."""
+    """Full recomputation at the Qwen2.5-7B widths with 9300 rows: two to three
+    rounds of whole 256 x 256 tiles, then 84 last rows as 128-row units
+    (test_gemm_plan.py). The oracle computes K/V for every row and the rest of
+    the layer on sampled rows, including the last rows."""
     import paper_2607_21599_amd as daf
     from oracle import get as oracle_get
     model, L_d, L_q = di.QWEN7B, 9236, 64
