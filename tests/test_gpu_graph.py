@@ -2,7 +2,8 @@
 
 The library's calls enqueue kernels and stream/event operations only (no
 allocation, no copy, no memset, no synchronisation), so a caller can capture a
-layer's attention into a graph; the layer call's second stream joins the
+layer's attention into a graph. Most layer calls run on the caller's stream; where
+the work tables do not fit one launch, the library's second stream joins the
 capture through its fork event and rejoins it through its join event. Each test
 captures once and replays several times. Between the replays the program
 restores the inputs it changes in place (hidden rows, the KV cache), scrambles
@@ -24,14 +25,17 @@ OUTS = ("o_imp", "lse_imp", "o_q", "lse_q", "hidden", "k_cache", "v_cache")
 REPLAYS = 4
 
 
-def _shape(name, L_d, L_q, n, seed):
-    return di.Shape(name, L_d=L_d, L_q=L_q, n=n, hq=28, hkv=4, d=128, dtype=di.BF16, seed=seed)
+def _shape(name, L_d, L_q, n, seed, dtype=di.BF16):
+    return di.Shape(name, L_d=L_d, L_q=L_q, n=n, hq=28, hkv=4, d=128, dtype=dtype, seed=seed)
 
 
 CASES = {
     "qwen7b_6k": lambda: di.workload("qwen7b_6k"),
     "ragged_batch": lambda: [_shape("r0", 3000, 77, 450, 81), _shape("r1", 700, 128, 700, 82),
                              _shape("r2", 5000, 5, 40, 83)],
+    # the layer call's second stream: 40 stage entries, and fp32 with 476 (128-row block, head) pairs
+    "twenty_requests": lambda: [_shape(f"t{i}", 300 + 40 * i, 3 + i, 30 + 5 * i, 90 + i) for i in range(20)],
+    "f32_two_streams": lambda: [_shape("f", 2500, 9, 2100, 120, di.F32)],
 }
 
 
@@ -90,7 +94,7 @@ def _replay_and_check(run: _Run, fn, what):
 
 @pytest.mark.parametrize("case", list(CASES))
 def test_layer_call_graph(case):
-    """gather + daf_layer_attn (two streams inside) captured as one graph."""
+    """gather + daf_layer_attn (one stream, or two inside) captured as one graph."""
     run = _Run(CASES[case]())
 
     def step():
