@@ -207,10 +207,11 @@ WsLayout ws_layout(const Cfg &c, const Batch &b, const std::vector<Split> &sp) {
 }
 
 // ---- second stream for the layer call ----------------------------------------
-// When one launch cannot hold both stages' work tables, daf_layer_attn runs
-// stage 1 on a library-owned stream (default priority),
-// forked from and joined back into the caller's stream by events, so that it
-// overlaps the KV write-back, stage 2 and the merge. One stream and two events
+// Where both stages do not go in one launch (one_launch: more than 32 stage
+// entries, or fp32 with more than kF32OneLaunchJobs stage-1 jobs), daf_layer_attn
+// runs stage 1 on a library-owned stream (default priority), forked from and
+// joined back into the caller's stream by events, so that it overlaps the KV
+// write-back, stage 2 and the merge. One stream and two events
 // per device, created on first use; the mutex keeps each call's fork and join
 // together when several threads enqueue at once.
 struct AuxStream {
@@ -352,7 +353,7 @@ daf_status_t run_entries(const Cfg &c, AttnKind kind, const std::vector<AttnEntr
 }
 
 // Whether the layer call runs both stages in one launch: their work tables fit
-// it (at most 16 requests with both stages). One launch needs no second stream
+// it (kMaxEntries, one per request and stage). One launch needs no second stream
 // (two events and two waits, about 20 us of host time and 6 + 5 us between
 // kernels), and the jobs of one stage fill in where the other's leave CUs idle:
 // 16k keys, n = 2458: 120 us on two streams, 105 in one launch; 32k, n = 4915
@@ -576,7 +577,8 @@ daf_status_t layer_attn_impl(const Cfg &c, const Batch &b, const int32_t *idx, c
     return ok();
   }
   std::lock_guard<std::mutex> lock(g_aux_mu);
-  AuxStream *ax = (self.empty() || !fork) ? nullptr : aux_stream();
+  // (without a question there is no stage 2 to run beside)
+  AuxStream *ax = (self.empty() || qdoc.attn.empty() || !fork) ? nullptr : aux_stream();
   daf_status_t st1 = DAF_OK;
   daf_status_t st = fuse_impl(c, b, DAF_FUSE_KV, idx, k_imp, v_imp, k_q, v_q, k_cache, v_cache, nullptr,
                               nullptr, nullptr, stream);

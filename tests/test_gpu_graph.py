@@ -36,6 +36,8 @@ CASES = {
     # the layer call's second stream: 40 stage entries, and fp32 with 476 (128-row block, head) pairs
     "twenty_requests": lambda: [_shape(f"t{i}", 300 + 40 * i, 3 + i, 30 + 5 * i, 90 + i) for i in range(20)],
     "f32_two_streams": lambda: [_shape("f", 2500, 9, 2100, 120, di.F32)],
+    # important tokens only: the caller's stream alone
+    "no_question": lambda: [_shape("n", 1500, 0, 260, 121)],
 }
 
 
