@@ -59,18 +59,21 @@
  * Asynchrony. Work is enqueued on `stream` (NULL = the default stream) and the
  *   call returns without synchronising. Calls are re-entrant and thread-safe;
  *   the only state the library keeps is daf_layer_attn's second stream and its
- *   two events per device (created on first use, guarded by a mutex; used by
- *   batches too large for one attention launch). Calls that write the same buffers must be ordered
- *   by the caller.
+ *   two events per device (created on first use, guarded by a mutex). Only calls
+ *   whose two stages do not go in one launch use them: those with more than 32
+ *   stage entries (one per request with important tokens, one per request with a
+ *   question), and fp32 calls whose stage 1 has more than 448 pairs of a 128-row
+ *   block and a query head. Calls that write the same buffers must be ordered by
+ *   the caller.
  * Graph capture. The calls enqueue kernels and event record/wait operations
  *   only (no allocation, copy, memset or synchronisation), so a sequence of
- *   them can be captured into a HIP graph and replayed. daf_layer_attn's
- *   second stream joins the capture through its fork event and rejoins the
- *   caller's stream before the call returns. Make the first daf_layer_attn
- *   call on a device outside any capture (it creates the stream and events),
- *   and make no daf_layer_attn call on that device from another stream or
- *   thread while such a capture is open: the shared second stream stays part
- *   of the capture until it ends.
+ *   them can be captured into a HIP graph and replayed. Where daf_layer_attn or
+ *   daf_decoder_layer uses the second stream (see Asynchrony), it joins the
+ *   capture through its fork event and rejoins the caller's stream before the
+ *   call returns. Make the first such call on a device outside any capture (it
+ *   creates the stream and events), and make no other such call on that device
+ *   from another stream or thread while its capture is open: the shared second
+ *   stream stays part of the capture until it ends.
  * Errors. Every host-visible precondition is checked before anything is
  *   enqueued; on failure the call returns a non-zero daf_status_t, enqueues
  *   nothing, and daf_last_error() describes the problem (thread-local). A
@@ -237,10 +240,10 @@ size_t daf_layer_workspace_size(const daf_attn_cfg_t *cfg,
 /* One DAF attention layer (Sec. 2 items 1-3), in the order the paper fixes:
  * hybrid KV write-back (DAF_FUSE_KV) first, then stage 2 (with its split
  * merge); stage 1 needs none of these and runs beside them: in the same launch
- * as stage 2, or for more than 16 requests on a stream the library owns (one
- * per device, default priority), forked from `stream` and joined back into it
- * with events. All of the call's work is ordered on `stream` for the caller. Arguments as in the stage calls. o_imp and o_q
- * receive the stage outputs; the same rows are written into `hidden` exactly
+ * as stage 2, or for large batches (see Asynchrony) on a stream the library owns
+ * (one per device, default priority), forked from `stream` and joined back into
+ * it with events. All of the call's work is ordered on `stream` for the caller.
+ * Arguments as in the stage calls. o_imp and o_q receive the stage outputs; the same rows are written into `hidden` exactly
  * as DAF_FUSE_HIDDEN would (the state fusion happens in the stage epilogues,
  * without a separate pass). */
 daf_status_t daf_layer_attn(const daf_attn_cfg_t *cfg, const daf_batch_t *batch,
