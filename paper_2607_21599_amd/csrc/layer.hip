@@ -98,8 +98,8 @@ __global__ __launch_bounds__(kRowThreads) void rope_rows_kernel(int64_t rows, in
   }
 }
 
-// The same for head sizes, strides or addresses that do not allow 16-byte
-// pieces: one thread per (row, i) rotates pair i of every head.
+// The same for few heads, and for head sizes, strides or addresses that do not
+// allow 16-byte pieces: one thread per (row, i) rotates pair i of every head.
 __global__ __launch_bounds__(kRowThreads) void rope_kernel(int64_t rows, int heads, int d, int64_t row_stride,
                                                            __bf16 *x, const int32_t *pos, double log2_theta) {
   const int half = d / 2;
@@ -154,7 +154,13 @@ hipError_t launch_rope(int64_t rows, int heads, int d, int64_t row_stride, void 
   if (rows <= 0 || heads <= 0) return hipSuccess;
   // 16-byte pieces of a half head: every piece of either tensor aligned
   auto whole = [&](const void *p, int64_t stride) { return reinterpret_cast<uintptr_t>(p) % 16 == 0 && stride % 8 == 0; };
-  if (d % 16 == 0 && d / 2 <= kRopeMaxHalf && whole(x, row_stride) && (!x2 || whole(x2, row_stride2))) {
+  // and enough of them per row to share its sines: one tensor with at most 8 heads
+  // of 512 features in all takes a thread per pair (32896 rows, pieces and threads:
+  // 1 x 64 10.7 and 7.5 us, 8 x 64 14.9 and 13.6, 4 x 128 17.9 and 16.2; 100000 rows
+  // of 4 x 16 21.7 and 8.8); with more heads that thread is the longer way (5043 rows
+  // of 16 x 32 4.5 and 5.7, 28 x 128 12 and 16), and two tensors would be two launches
+  const bool few = !x2 && heads <= 8 && heads * d <= 512;
+  if (!few && d % 16 == 0 && d / 2 <= kRopeMaxHalf && whole(x, row_stride) && (!x2 || whole(x2, row_stride2))) {
     const RopeTensors t{{static_cast<__bf16 *>(x), static_cast<__bf16 *>(x2)}, {heads, x2 ? heads2 : 0},
                         {row_stride, row_stride2}};
     rope_rows_kernel<<<dim3((unsigned)((rows + kRopeRows - 1) / kRopeRows)), dim3(kRowThreads), 0, st>>>(

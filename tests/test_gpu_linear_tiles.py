@@ -66,7 +66,8 @@ def test_swiglu_tiles(M, I, K):
 
 
 @pytest.mark.parametrize("rows,heads,d,stride,shift", [
-    (1, 1, 16, 16, 0), (5, 3, 64, 192, 0), (257, 28, 128, 4608, 0), (9, 2, 256, 520, 0),  # 16-byte pieces
+    (257, 28, 128, 4608, 0), (1, 9, 16, 144, 0), (6, 9, 64, 640, 0), (9, 3, 256, 776, 0),  # 16-byte pieces
+    (1, 1, 16, 16, 0), (5, 3, 64, 192, 0), (9, 2, 256, 520, 0), (33, 8, 64, 512, 0), (10, 5, 128, 640, 0),  # few heads, and above
     (7, 3, 64, 196, 0), (6, 2, 128, 256, 1), (3, 2, 24, 48, 0), (4, 1, 512, 512, 0)])     # stride, address, sizes
 def test_rope_paths(rows, heads, d, stride, shift):
     """Both rope kernels on either side of the rule that picks them; the rest
