@@ -590,6 +590,8 @@ hipError_t launch_gemm_job(const GemmJob &job, float *part, size_t part_bytes, h
   p.j = job;
   p.part = part;
   if (job.M <= 0 || job.n_segs <= 0) return hipSuccess;
+  if (!job.glu && part == nullptr && job.n_segs == 1 && small_tiles_pay(job.M, job.seg[0].N, job.K))
+    return launch_gemm_small(job, st);
   plan_job(p, part_bytes);
   const int blocks = kXcds * ((p.n_full + kXcds - 1) / kXcds + (p.n_half * p.k_parts + kXcds - 1) / kXcds);
   if (job.glu) gemm_bf16_kernel<true><<<dim3(blocks), dim3(512), 0, st>>>(p);

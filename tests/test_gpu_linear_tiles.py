@@ -1,9 +1,11 @@
 """GPU: the projections at the edges of their tiling, and the rotary embedding on
 either side of its vector rule, against the CPU oracle.
 
-256-row and 128-row tiles, ragged last rows on either side of 128, column
-counts that end inside a 256-column tile, one, odd and even k step counts, and
-launches with whole tiles before cut ones (more than 256 tiles). Outputs are
+Ragged last rows on either side of 128, column counts that end inside a
+256-column tile, one, odd and even k step counts, and launches with whole tiles
+before cut ones (more than 256 tiles of 256 rows). daf_linear runs all but its two
+largest sizes here in 128 x 128 tiles; test_gpu_linear_small.py has such edges for
+the 256-row kernel, and so has the gated product. Outputs are
 bf16 of order-1 values: half a bf16 ulp (2^-9 relative) plus fp32 accumulation,
 checked as |gpu - oracle| <= 2^-8 |oracle| + 2e-3."""
 from __future__ import annotations
@@ -35,7 +37,6 @@ def _check(got, ref, what):
     (700, 2304, 128, True, False),
     # 272 tiles of 256 rows: 256 whole, 16 cut in two, then one row range of 104 or none
     (4200, 4352, 64, True, True), (4226, 4096, 192, False, True),
-    # 20 x 8 tiles, more than half a round: every tile whole, 14 last rows
     (5134, 2048, 128, True, False)])
 def test_linear_tiles(M, N, K, bias, res):
     import paper_2607_21599_amd as daf
