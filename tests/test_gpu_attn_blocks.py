@@ -1,10 +1,10 @@
 """GPU: stage 1 on either side of the block-height rule, against the oracle.
 
-Launches of up to 448 (128-row block, head) pairs run 64-row blocks, larger
-ones 128-row blocks: row counts just below and above the line for several head
-shapes, sizes that end inside a block, a ragged batch, and queries and keys
-that make the running reference rise late (each loud key 40 log2 units above
-the one before). The bars are those of tests/parity.py."""
+Launches of up to 448 (128-row block, head) pairs (D = 64: 544; see
+test_gpu_position_blocks.py) run 64-row blocks, larger ones 128-row blocks: row
+counts just below and above the line for several head shapes, sizes that end
+inside a block, a ragged batch, and queries and keys that make the running
+reference rise late (each loud key 40 log2 units above the one before). The bars are those of tests/parity.py."""
 from __future__ import annotations
 
 import numpy as np
