@@ -72,6 +72,12 @@ constexpr int kBN = 64;                  // keys per tile
 // 2^28 (kLimit, its bf16 bits; at most 2^32 per 16 keys) is the exact max taken,
 // the reference raised and the probabilities formed again.
 constexpr unsigned kLimit = (127 + 28) << 7;
+// A split of at most kShortSplit tiles (stage 2 with few key tiles per workgroup,
+// whose splits would otherwise be half as long) raises it past 2^6: the LSE's error
+// against 64 bits (1473 keys, 243 rows, 8 heads of 64) is 1.03e-5 with one tile per
+// split, with two 1.05e-5 at 2^28 and 1.01e-5 at 2^6; stage 2 takes 0-2% longer.
+constexpr unsigned kShortLimit = (127 + 6) << 7;
+constexpr int kShortSplit = 10;
 constexpr float kMaskedSlack = 8.0f;    // growth (log2) of a row's max that raises the reference in a masked tile
 constexpr float kNoReference = -3e38f;  // before the first key: every visible one's probability is infinite
 
@@ -199,6 +205,7 @@ struct WaveState {
   int wave_last_key;       // keys above this are masked for every row of the wave
   int wave_first_limit;    // keys up to this are visible to every row of the wave
   float sl2;
+  unsigned p_limit;        // bf16 bits of the probability that raises the reference
 };
 
 // Scores of one 32-key half tile: [16-key block][row block], D^T blocks: a
@@ -235,8 +242,8 @@ __device__ __forceinline__ unsigned softmax_half(const WaveState<D, NB> &w, cons
   }
   return top;
 }
-__device__ __forceinline__ bool out_of_range(unsigned top) {
-  return __builtin_amdgcn_ballot_w64(top >= kLimit << 16 || (unsigned short)top >= kLimit) != 0;
+__device__ __forceinline__ bool out_of_range(unsigned top, unsigned limit) {
+  return __builtin_amdgcn_ballot_w64(top >= limit << 16 || (top & 0xffffu) >= limit) != 0;
 }
 
 // O^T += V^T P^T over the 32 keys of one half tile. Contraction slot 8 g + j of
@@ -288,7 +295,7 @@ __device__ __forceinline__ void half_max(const WaveState<D, NB> &w, const Scores
 // and again after raising it if one of them is out of range.
 template <int D, int NB>
 __device__ __forceinline__ void finish_half(WaveState<D, NB> &w, const Scores<NB> &sc, bf16x8 (&pf)[NB], unsigned top) {
-  if (out_of_range(top)) {
+  if (out_of_range(top, w.p_limit)) {
     float mt[NB];
     half_max<D, NB>(w, sc, mt);
     raise_to<D, NB>(w, mt);
@@ -514,6 +521,7 @@ __device__ __forceinline__ void attn_job(const AttnLaunch &p, const AttnList &l,
   w.quad = quad;
   w.wave = wave;
   w.sl2 = p.scale_log2;
+  w.p_limit = KIND == 1 && E.split_keys <= kShortSplit * kBN ? kShortLimit : kLimit;
 #pragma unroll
   for (int nb = 0; nb < NB; ++nb) {
     w.m_run[nb] = kNoReference;
